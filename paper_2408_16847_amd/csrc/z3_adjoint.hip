@@ -181,6 +181,7 @@ struct ScatterArgs {
     // map blockIdx.y: pv and grad advance by n_stride, rec by rec_stride, D by d_stride
     size_t n_stride, rec_stride, d_stride;
     double px0, py0, psx;         // plane: origin and cell-coordinate scale
+    BinGroups groups;             // bins of each blockIdx.z
 };
 
 // Pivot on a plane: strip coordinate y - y0 in place of the colatitude, fixed frame
@@ -228,7 +229,7 @@ void k_adjoint_scatter(ScatterArgs a)
     const bool valid = p < a.p1;
     const int64_t pp = valid ? p : a.p1 - 1;
     const size_t mp0 = (size_t)blockIdx.y * K;  // first map of this block
-    a.rec += mp0 * a.rec_stride;  // positions (the same for every map)
+    const double4 *rec = a.rec + mp0 * a.rec_stride;  // positions (the same for every map)
     const PivotFrame f = PLANAR ? plane_frame(a.px[pp], a.py[pp], a.pz[pp], a.py0)
                                 : pivot_frame(a.px[pp], a.py[pp], a.pz[pp]);
     const double phd = PLANAR ? (a.px[pp] - a.px0) * a.psx : 0.0;
@@ -239,7 +240,9 @@ void k_adjoint_scatter(ScatterArgs a)
     const int nb = a.nb;
     const bool unit_w = a.wdbl == nullptr;
 
-    for (int bin = 0; bin < nb; ++bin) {
+    const int grp = a.groups.n - 1 - (int)blockIdx.z;  // outermost bins first
+    const int bin_end = a.groups.first[grp + 1];
+    for (int bin = a.groups.first[grp]; bin < bin_end; ++bin) {
         const double elo = a.edges->e[bin], ehi = a.edges->e[bin + 1];
         const double hav_out = a.edges->hav_out[bin + 1], hav_in = a.edges->hav_in[bin];
         int klo, khi;
@@ -286,7 +289,7 @@ void k_adjoint_scatter(ScatterArgs a)
                 if (jhi <= jlo) continue;
                 const bool use_lds = jhi - jlo <= SLOTS;
                 for (; j < jend; ++j) {
-                    const double4 r = a.rec[j];
+                    const double4 r = rec[j];
                     const double dx = r.x - f.xp, dy = r.y - f.yp, dz = r.z - f.zp;
                     const double d2 = (dx * dx + dy * dy) + dz * dz;
                     if (d2 >= elo && d2 < ehi) {
@@ -363,10 +366,10 @@ template <int M>
 static void launch_scatter_m(const ScatterArgs &a, int nm, bool planar, hipStream_t s)
 {
     if (planar) {  // one map per lane, one grid row per map
-        hipLaunchKernelGGL((k_adjoint_scatter<M, 1, true>), dim3(a.nblocks, nm), dim3(kBlock), 0, s, a);
+        hipLaunchKernelGGL((k_adjoint_scatter<M, 1, true>), dim3(a.nblocks, nm, a.groups.n), dim3(kBlock), 0, s, a);
         return;
     }
-    if (nm >= 4) hipLaunchKernelGGL((k_adjoint_scatter<M, 4>), dim3(a.nblocks, nm / 4), dim3(kBlock), 0, s, a);
+    if (nm >= 4) hipLaunchKernelGGL((k_adjoint_scatter<M, 4>), dim3(a.nblocks, nm / 4, a.groups.n), dim3(kBlock), 0, s, a);
     if (nm & 2) {
         ScatterArgs b = a;
         const size_t first = (size_t)(nm & ~3);
@@ -374,7 +377,7 @@ static void launch_scatter_m(const ScatterArgs &a, int nm, bool planar, hipStrea
         b.grad += first * a.n_stride;
         b.rec += first * a.rec_stride;
         b.D += first * a.d_stride;
-        hipLaunchKernelGGL((k_adjoint_scatter<M, 2>), dim3(a.nblocks, 1), dim3(kBlock), 0, s, b);
+        hipLaunchKernelGGL((k_adjoint_scatter<M, 2>), dim3(a.nblocks, 1, a.groups.n), dim3(kBlock), 0, s, b);
     }
     if (nm & 1) {
         ScatterArgs b = a;
@@ -383,7 +386,7 @@ static void launch_scatter_m(const ScatterArgs &a, int nm, bool planar, hipStrea
         b.grad += last * a.n_stride;
         b.rec += last * a.rec_stride;
         b.D += last * a.d_stride;
-        hipLaunchKernelGGL((k_adjoint_scatter<M, 1>), dim3(a.nblocks, 1), dim3(kBlock), 0, s, b);
+        hipLaunchKernelGGL((k_adjoint_scatter<M, 1>), dim3(a.nblocks, 1, a.groups.n), dim3(kBlock), 0, s, b);
     }
 }
 
@@ -438,6 +441,7 @@ static z3_status adjoint_chunk_maps(z3_index idx, int map, int nm, int m_max, in
     sa.n_stride = (size_t)idx->n;
     sa.rec_stride = (size_t)2 * idx->n;
     sa.d_stride = stride;
+    sa.groups = bin_groups(idx, sa.nblocks);
     sa.px0 = idx->plane_x0; sa.py0 = idx->plane_y0; sa.psx = idx->plane_sx;
     switch (m_max) {
 #define Z3_CASE(MM) case MM: launch_scatter_m<MM>(sa, nm, idx->planar, s); break;

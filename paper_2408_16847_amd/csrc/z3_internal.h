@@ -140,6 +140,16 @@ z3_status update_values_impl(z3_index idx, const double *x, hipStream_t s);
 z3_status set_values_impl(z3_index idx, int nmaps, const double *x, hipStream_t s);
 void free_index(z3_index idx);
 
+// Radial bins of a launch split over gridDim.y.  A block of pivots visits its bins one after
+// the other and the bins are independent of each other, so a launch of few pivot blocks fills
+// the chip by giving each block a contiguous group of bins.  `first[g]` is group g's first
+// bin; the kernels take the groups from the outermost (longest) to the innermost.
+struct BinGroups {
+    int n;
+    unsigned char first[Z3_MAX_NBINS + 1];
+};
+BinGroups bin_groups(const z3_index_s *idx, int64_t nblk);
+
 // multipole kernels (z3_multipoles.hip)
 // Pivot positions: either the index's own points (index order) or an external catalogue.
 struct Pivots {

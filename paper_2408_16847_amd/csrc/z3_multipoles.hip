@@ -73,7 +73,36 @@ struct MultArgs {
     double px0, py0, psx;         // PLANAR: plane origin and cell-coordinate scale
     double tiny;                  // kBearingTiny, passed so that it sits in scalar registers
     int nblocks;
+    BinGroups groups;             // bins of each blockIdx.y
 };
+
+// Groups of bins for a launch of nblk pivot blocks.  Up to kFillBlocks blocks in all (eight per
+// resident slot, 256 CUs x 4 blocks): with fewer, SIMDs idle (20,000 pivots are 79 blocks) or a
+// last round of long blocks runs on a part of the chip (490,000 pivots are 1.9 rounds); with
+// more, the pivot set-up each group repeats costs more than the balance gives.  The groups
+// are cut where the running cost of the bins passes each g / n of the total; a bin costs its
+// pairs (its share of the annuli's area) and the band windows that even a sparse bin visits.
+// Measured, one launch without and with the split: 4,000 pivots x 10 bins 528 -> 103 us, 20,000
+// x 10 1342 -> 293 us, 150,000 x 15 3682 -> 2414 us, a plane of 491,000 x 15 3196 -> 2875 us,
+// 786,000 x 15 2893 -> 2677 us; four maps per lane, 197,000 x 12, 1569 -> 1076 us.
+constexpr int64_t kFillBlocks = 8192;
+
+BinGroups bin_groups(const z3_index_s *idx, int64_t nblk)
+{
+    const int nb = idx->nbins;
+    const int64_t want = nblk > 0 ? (kFillBlocks + nblk - 1) / nblk : 1;
+    BinGroups q;
+    q.n = (int)(want < nb ? want : nb);
+    const double *e = idx->edges.e;
+    double run = 0.0;
+    for (int b = 0, g = 0; b < nb; ++b) {
+        // a group starts here when its share is reached, or when every bin left must start one
+        if (g < q.n && (run >= 1.5 * g / q.n || nb - b == q.n - g)) q.first[g++] = (unsigned char)b;
+        run += (e[b + 1] - e[b]) / (e[nb] - e[0]) + 0.5 / nb;
+    }
+    q.first[q.n] = (unsigned char)nb;
+    return q;
+}
 
 // Occupancy target of the multipole kernel (waves per SIMD that the register allocation
 // aims for).  Measured on MI355X at m_max = 10: 4 waves beat 3 by ~15% despite a couple
@@ -161,7 +190,9 @@ void k_multipoles(MultArgs a)
     const bool unit_w = a.wdbl == nullptr;
     uint64_t my_pairs = 0;
 
-    for (int bin = 0; bin < nb; ++bin) {
+    const int grp = a.groups.n - 1 - (int)blockIdx.y;  // outermost bins first
+    const int bin_end = a.groups.first[grp + 1];
+    for (int bin = a.groups.first[grp]; bin < bin_end; ++bin) {
         const double elo = a.edges->e[bin], ehi = a.edges->e[bin + 1];
         double hav_out = a.edges->hav_out[bin + 1], hav_in = a.edges->hav_in[bin];
         double rad = a.edges->rad_out[bin + 1];
@@ -342,6 +373,7 @@ struct MapArgs {
     double *W;                    // [nb][ldA] W_{p,b} (shared by the maps), or null
     uint64_t *pair_total;
     int nblocks;
+    BinGroups groups;             // bins of each blockIdx.y
 };
 
 template <int M>
@@ -390,7 +422,9 @@ void k_multipoles_maps(MapArgs a)
     const bool unit_w = a.wdbl == nullptr;
     uint64_t my_pairs = 0;
 
-    for (int bin = 0; bin < nb; ++bin) {
+    const int grp = a.groups.n - 1 - (int)blockIdx.y;  // outermost bins first
+    const int bin_end = a.groups.first[grp + 1];
+    for (int bin = a.groups.first[grp]; bin < bin_end; ++bin) {
         const double elo = a.edges->e[bin], ehi = a.edges->e[bin + 1];
         const double hav_out = a.edges->hav_out[bin + 1], hav_in = a.edges->hav_in[bin];
         const double rad = a.edges->rad_out[bin + 1];
@@ -498,7 +532,7 @@ void k_multipoles_maps(MapArgs a)
 template <int M>
 static void launch_maps_m(bool f32out, bool three, const MapArgs &a, hipStream_t s)
 {
-    dim3 grid(a.nblocks), block(kBlock);
+    dim3 grid(a.nblocks, a.groups.n), block(kBlock);
     if (three) {
         if (f32out) hipLaunchKernelGGL((k_multipoles_maps<M, true, 3>), grid, block, 0, s, a);
         else hipLaunchKernelGGL((k_multipoles_maps<M, false, 3>), grid, block, 0, s, a);
@@ -531,6 +565,7 @@ z3_status launch_multipoles_maps(const z3_index_s *idx, int group, int nslots, i
     a.W = W;
     a.pair_total = pair_total;
     a.nblocks = (int)nblk;
+    a.groups = bin_groups(idx, nblk);
     const bool f32 = prec == Z3_PREC_MIXED;
     hipEvent_t ev0;
     profile_begin(s, &ev0);
@@ -551,7 +586,7 @@ z3_status launch_multipoles_maps(const z3_index_s *idx, int group, int nslots, i
 template <int M, bool PLANAR>
 static void launch_mp(bool f32out, bool ids, bool self, const MultArgs &a, hipStream_t s)
 {
-    dim3 grid(a.nblocks), block(kBlock);
+    dim3 grid(a.nblocks, a.groups.n), block(kBlock);
     if (f32out) {
         if (ids) hipLaunchKernelGGL((k_multipoles<M, true, true, false, PLANAR>), grid, block, 0, s, a);
         else if (self) hipLaunchKernelGGL((k_multipoles<M, true, false, true, PLANAR>), grid, block, 0, s, a);
@@ -598,6 +633,7 @@ z3_status launch_multipoles(const z3_index_s *idx, Pivots piv, int map, int m_ma
     a.px0 = idx->plane_x0; a.py0 = idx->plane_y0; a.psx = idx->plane_sx;
     a.tiny = kBearingTiny;
     a.nblocks = (int)nblk;
+    a.groups = bin_groups(idx, nblk);
     const bool mixed = prec == Z3_PREC_MIXED, ids = idhash != nullptr, self = self_part != nullptr;
     hipEvent_t ev0;
     profile_begin(s, &ev0);
