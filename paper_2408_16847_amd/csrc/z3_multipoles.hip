@@ -19,14 +19,10 @@
 //
 // Harmonics: the paper's remark after the binned estimator builds cos(m phi) and
 // sin(m phi) from Chebyshev polynomials of cos(phi), so that no trigonometric function is
-// evaluated per pair.  Here one second-kind chain per pair, u_k = v U_k(c) with
-// U_k = 2 c U_{k-1} - U_{k-2} (c = cos phi, v = w_j x_j), feeds two sums per bin:
-//   SU_k = sum u_k  and  SV_k = sum 2 sin(phi) u_k,
-// and the bin's epilogue forms Y_m = (SU_m - SU_{m-2}) / 2 (T_m = (U_m - U_{m-2}) / 2,
-// U_{-1} = 0) and Z_m = SV_{m-1} / 2 (sin(m phi) = sin(phi) U_{m-1}(c)).  Per pair and m:
-// one FMA of the chain, one add and one FMA into the sums, against two FMAs and two adds
-// for separate first- and second-kind chains.  Near phi = 0 or pi, U_m ~ m + 1 and the
-// difference gives up ~log2(m) bits: ~1e-14 of sum |v| at m = 10 in FP64.
+// evaluated per pair.  The 2 M + 1 sums of a bin need a basis of the trigonometric
+// polynomials of degree M, not the harmonics themselves; HarmonicSums takes products of two
+// short factors, whose sums cost one FMA each and whose factors are few (see there), and the
+// bin's epilogue turns the sums into Y_m and Z_m by the product-to-sum identities.
 //
 // Pivots on a plane (PLANAR): the same loop over a strip x cell grid of (x, y, 0) records;
 // the frame is fixed (angles from +y towards +x) and the windows are planar_window's.
@@ -104,16 +100,96 @@ BinGroups bin_groups(const z3_index_s *idx, int64_t nblk)
     return q;
 }
 
+// Sums over a bin's pairs of v times a basis of the trigonometric polynomials of degree <= M,
+// v = w_j x_j.  With B_0 = 1, B_k = 2 T_k(cos phi) = 2 cos(k phi) (B_1 = t = 2 cos phi, B_2 = t t - 2,
+// B_{k+1} = t B_k - B_{k-1}) and s = 2 sin phi the basis is
+//   B_0..B_H,  B_H B_1..B_H B_{M-H},  s B_0..s B_{H-1},  s B_H B_0..s B_H B_{M-H-1},
+// from H - 1 steps of the chain and the three weights v B_H, v s and v s B_H: H + 2 operations
+// a pair beside the 2 M + 1 additions into the sums that any method needs, against M for one
+// chain over all degrees (31 -> 28 FP64 instructions a pair at M = 10, 49 -> 43 at M = 16).
+// H = ceil(M / 2); up to M = 4 the products save nothing and H = M leaves them out.  finish()
+// recovers the harmonics from
+//   B_H B_j = 2 (T_{H+j} + T_{H-j})  and  s B_k = 2 (sin (k+1) phi - sin (k-1) phi):
+// every step adds sums of size sum |v| with factors of 1 or 1/2, so no bits are lost near
+// phi = 0 and pi as in the second-kind basis (U_m ~ m + 1 there).  Measured against that one
+// chain: Nside 512 at M = 16 65.6 -> 58.0 ms a launch (with 3 waves per SIMD in place of 2),
+// half of Nside 1024 at M = 10 160.5 -> 156.7 ms, 786,000 pivots at M = 10 2669 -> 2617 us.
+template <int M>
+struct HarmonicSums {
+    static constexpr int H = M <= 4 ? M : (M + 1) / 2;
+    static constexpr int R = M - H;
+    double c[M + 1];  // B_k (k <= H), B_H B_j at H + j
+    double s[M + 1];  // s B_{k-1} at k (1 <= k <= H), s B_H B_j at H + 1 + j
+
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll
+        for (int m = 0; m <= M; ++m) { c[m] = 0.0; s[m] = 0.0; }
+    }
+
+    // one pair: tc = 2 cos phi, ts = 2 sin phi
+    __device__ __forceinline__ void add(double v, double tc, double ts)
+    {
+        c[0] += v;
+        if constexpr (M >= 1) {
+            double B[H + 1];
+            B[1] = tc;
+            if constexpr (H >= 2) B[2] = fma(tc, tc, -2.0);
+#pragma unroll
+            for (int k = 3; k <= H; ++k) B[k] = fma(tc, B[k - 1], -B[k - 2]);
+            const double vs = v * ts;
+            s[1] += vs;
+#pragma unroll
+            for (int k = 1; k < H; ++k) {
+                c[k] = fma(v, B[k], c[k]);
+                s[k + 1] = fma(vs, B[k], s[k + 1]);
+            }
+            if constexpr (R == 0) {
+                c[H] = fma(v, B[H], c[H]);
+            } else {
+                const double vg = v * B[H], vsg = vs * B[H];
+                c[H] += vg;
+                s[H + 1] += vsg;
+#pragma unroll
+                for (int j = 1; j <= R; ++j) {
+                    c[H + j] = fma(vg, B[j], c[H + j]);
+                    if (j < R) s[H + 1 + j] = fma(vsg, B[j], s[H + 1 + j]);
+                }
+            }
+        }
+    }
+
+    // c[m] = sum v cos(m phi), s[m] = sum v sin(m phi)
+    __device__ __forceinline__ void finish()
+    {
+#pragma unroll
+        for (int k = 1; k <= H; ++k) {
+            c[k] *= 0.5;
+            s[k] = k >= 2 ? fma(0.5, s[k], s[k >= 2 ? k - 2 : 0]) : 0.5 * s[k];
+        }
+#pragma unroll
+        for (int j = 1; j <= R; ++j) c[H + j] = fma(0.5, c[H + j], -c[H - j]);
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            // s_{H+1+j} = S / 2 + s_{H+j-1} - s_{H-j+1} + s_{H-j-1}, the last two for j >= 1
+            double t = fma(0.5, s[H + 1 + j], s[H + j - 1]);
+            if (j >= 1) t = t - s[H - j + 1] + s[H - j - 1];
+            s[H + 1 + j] = t;
+        }
+    }
+};
+
 // Occupancy target of the multipole kernel (waves per SIMD that the register allocation
 // aims for).  Measured on MI355X at m_max = 10: 4 waves beat 3 by ~15% despite a couple
-// of spilled registers; larger m_max needs more accumulators, so the target drops.
+// of spilled registers; from m_max = 11 the sums need more registers, and 3 waves hold them
+// without spills up to m_max = 16.
 #ifndef Z3_MULT_WAVES_PER_EU
 #define Z3_MULT_WAVES_PER_EU 4
 #endif
 template <int M>
 constexpr int mult_waves_per_eu()
 {
-    return M <= 10 ? Z3_MULT_WAVES_PER_EU : (M <= 13 ? 3 : 2);
+    return M <= 10 ? Z3_MULT_WAVES_PER_EU : 3;
 }
 
 template <int M, bool F32OUT, bool IDS, bool SELF, bool PLANAR>
@@ -211,10 +287,8 @@ void k_multipoles(MultArgs a)
         klo = __builtin_amdgcn_readfirstlane(wave_min(klo));
         khi = __builtin_amdgcn_readfirstlane(wave_max(khi));
 
-        // SU_k = sum v U_k(cos phi) for k <= M, SV_k = sum v 2 sin(phi) U_k(cos phi) for k < M
-        double SU[M + 1], SV[M + 1];
-#pragma unroll
-        for (int m = 0; m <= M; ++m) { SU[m] = 0.0; SV[m] = 0.0; }
+        HarmonicSums<M> sums;
+        sums.clear();
         // wpend: the weight of the lane's previous pair, added at its next pair (or after the
         // bin), so that its load overlaps a candidate's work instead of stalling the pair that
         // requested it; the additions keep their order
@@ -273,21 +347,7 @@ void k_multipoles(MultArgs a)
                             const double u2 = PLANAR ? dx : fma(dx, ex, dy * ey);
                             double tc, ts;  // 2 cos(phi), 2 sin(phi)
                             twice_unit_bearing(u1, u2, a.tiny, tc, ts);
-                            SU[0] += v;
-                            if constexpr (M >= 1) {
-                                // one chain v U_k(cos phi): SU_k takes it, SV_k takes it
-                                // times 2 sin(phi)
-                                double ua = v, ub = tc * v;
-                                SV[0] = fma(ts, v, SV[0]);
-                                SU[1] += ub;
-#pragma unroll
-                                for (int k = 2; k <= M; ++k) {
-                                    SV[k - 1] = fma(ts, ub, SV[k - 1]);
-                                    const double uk = fma(tc, ub, -ua);
-                                    SU[k] += uk;
-                                    ua = ub; ub = uk;
-                                }
-                            }
+                            sums.add(v, tc, ts);
                         }
                     };
                     double4 ra = load_record(rband, off < oend ? off : 0u);
@@ -311,13 +371,11 @@ void k_multipoles(MultArgs a)
             if (a.norm == Z3_NORM_BIN) inv = Wb > 0.0 ? 1.0 / Wb : 0.0;
             if constexpr (SELF) self_t = a.pv[p] * Qb * inv * inv;
             if (a.A) {
-                // T_m = (U_m - U_{m-2}) / 2 (U_{-1} = 0) and sin(m phi) = sin(phi) U_{m-1}
-                const double hinv = 0.5 * inv;
+                sums.finish();
 #pragma unroll
                 for (int m = 0; m <= M; ++m) {
-                    const double y = m >= 2 ? SU[m] - SU[m >= 2 ? m - 2 : 0] : SU[m];
-                    const double re = m == 0 ? y * inv : y * hinv;
-                    const double im = m == 0 ? 0.0 : -SV[m >= 1 ? m - 1 : 0] * hinv;
+                    const double re = sums.c[m] * inv;
+                    const double im = m == 0 ? 0.0 : -sums.s[m] * inv;
                     const size_t ore = ((size_t)(2 * m) * nb + bin) * (size_t)a.ldA + col;
                     const size_t oim = ((size_t)(2 * m + 1) * nb + bin) * (size_t)a.ldA + col;
                     if constexpr (F32OUT) {
@@ -353,7 +411,8 @@ void k_multipoles(MultArgs a)
 // carries K maps of a group of kMapGroup (K = 3 when the caller reads at most the first three,
 // else 4): the pair test, the bearing and the unit chain U_k(cos phi) are computed once per
 // pair, and each map adds v U_k and v 2 sin(phi) U_k with two FMAs per k (the epilogue forms
-// the harmonics' sums as in k_multipoles).
+// the harmonics' sums from T_m = (U_m - U_{m-2}) / 2 and sin(m phi) = sin(phi) U_{m-1}; the
+// product basis of HarmonicSums would cost each map two more multiplications a pair).
 
 struct MapArgs {
     const double *px, *py, *pz;   // index-order pivot positions
@@ -435,8 +494,8 @@ void k_multipoles_maps(MapArgs a)
         klo = __builtin_amdgcn_readfirstlane(wave_min(klo));
         khi = __builtin_amdgcn_readfirstlane(wave_max(khi));
 
-        // per map: SU_k = sum v U_k(cos phi), SV_k = sum v 2 sin(phi) U_k(cos phi), as in
-        // k_multipoles, with one unit chain U_k shared by the maps
+        // per map: SU_k = sum v U_k(cos phi), SV_k = sum v 2 sin(phi) U_k(cos phi), with one unit
+        // chain U_k shared by the maps
         double SU[K][M + 1], SV[K][M + 1];
 #pragma unroll
         for (int k = 0; k < K; ++k)
