@@ -978,7 +978,7 @@ Z3_API z3_status z3_estimate_maps(z3_index idx, int m_max, int prec, int64_t p0,
         chunk = (chunk / kBlock) * kBlock;
         if (chunk < 4 * kBlock) chunk = 4 * kBlock;
         if (chunk > p1 - p0) chunk = p1 - p0;
-        const size_t pbytes = contract_partial_bytes(chunk, m_max, idx->nbins) * idx->nmaps;
+        const size_t pbytes = contract_partial_bytes(chunk, m_max, idx->nbins, idx->nmaps);
         void *wa = nullptr, *wst = nullptr, *wp = nullptr;
         st = scratch_alloc(&wst, (size_t)idx->nmaps * chunk * per_map_piv, s);
         if (st == Z3_OK && !direct) st = scratch_alloc(&wa, (size_t)idx->nmaps * chunk * per_map_piv, s);
@@ -1006,7 +1006,7 @@ Z3_API z3_status z3_estimate_maps(z3_index idx, int m_max, int prec, int64_t p0,
     if (chunk < 16 * kBlock) chunk = 16 * kBlock;
     if (chunk > p1 - p0) chunk = ((p1 - p0 + kBlock - 1) / kBlock) * kBlock;
     const size_t map_stride = (size_t)chunk * (m_max + 1) * 2 * idx->nbins;  // elements
-    size_t pbytes = contract_partial_bytes(chunk, m_max, idx->nbins) * kMapGroup;
+    size_t pbytes = contract_partial_bytes(chunk, m_max, idx->nbins, kMapGroup);
     void *wa = nullptr, *wp = nullptr;
     if ((st = scratch_alloc(&wa, (size_t)kMapGroup * chunk * per_map_piv, s)) != Z3_OK) return st;
     if ((st = scratch_alloc(&wp, pbytes, s)) != Z3_OK) {

@@ -8,8 +8,9 @@
 // of pivots with v_mfma_f64_16x16x4f64 (FP64 path) or v_mfma_f32_16x16x4f32 (mixed path: FP32
 // multipoles U; the scaled operand v_p U_i is formed in FP64 and split into FP32 hi + lo
 // parts, two MFMAs per step; FP32 sums over 16 pivots are added into FP64 segment sums),
-// from tiles of pivots staged in LDS (k_pair_lds for the pivot-minor layout of the one-map
-// kernels, k_gram_lds for the many-map kernel's pivot-major staging).
+// from the pivot-minor layout of the one-map kernels (through LDS, k_pair_lds; on the mixed path
+// up to 32 bins straight into registers, k_pair), or from the many-map kernel's pivot-major
+// staging through LDS (k_gram_lds).
 // Only tiles on or above the diagonal are formed; entries below are read from their
 // mirror, so zeta(b2, b1) is exactly conj(zeta(b1, b2)) and Im zeta(b, b) is exactly 0.
 // Segment partials are summed in FP64 in segment order (deterministic).
@@ -20,18 +21,72 @@
 
 namespace z3 {
 
-constexpr int kSeg = 4096;  // pivots per contraction wave
+// Pivots per segment: at most kSeg (a partial sum of 2 KB a tile pair is then small beside the
+// pivots it sums), fewer when the launch would leave the chip idle (one block per segment and
+// m: 20,000 pivots at m_max = 8 were 45 blocks of 4096 pivots, 146 us).  kContractUnits bounds
+// the partial sums, (segment, map, m, tile pair), that shorter segments may bring, to 16 MB.
+constexpr int kSeg = 4096, kSegMin = 128;
+constexpr int kContractUnits = 8192;
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 static inline int tiles_for(int nbins) { return (2 * nbins + 15) / 16; }
 
-size_t contract_partial_bytes(int64_t npiv, int m_max, int nbins)
+// Pivots per segment for npiv pivots and `units` (map, m, tile pair) per segment: a multiple of
+// kSegMin.
+static int segment_pivots(int64_t npiv, int64_t units)
+{
+    const int64_t most = std::max<int64_t>(1, kContractUnits / units);  // segments the bound allows
+    const int64_t len = (npiv + most - 1) / most;
+    return (int)std::min<int64_t>(kSeg, (len + kSegMin - 1) / kSegMin * kSegMin);
+}
+
+// Partial sums (segment, unit) of any call with up to npiv pivots and up to `units` per segment
+// (a call's last chunk is shorter, its last group of maps smaller).
+static size_t most_partials(int64_t npiv, int64_t units)
+{
+    const int64_t longest = (npiv + kSeg - 1) / kSeg, shortest = (npiv + kSegMin - 1) / kSegMin;
+    const int64_t n = std::max(longest * units, std::min(shortest * units, std::max<int64_t>(kContractUnits, units)));
+    return (size_t)std::max(n, units);
+}
+
+size_t contract_partial_bytes(int64_t npiv, int m_max, int nbins, int nmaps)
 {
     const int T = tiles_for(nbins);
-    const int64_t nseg = (npiv + kSeg - 1) / kSeg;
-    return (size_t)(nseg > 0 ? nseg : 1) * (size_t)(m_max + 1) * (size_t)(T * (T + 1) / 2) * 256 * sizeof(double);
+    return most_partials(npiv, (int64_t)nmaps * (m_max + 1) * (T * (T + 1) / 2)) * 256 * sizeof(double);
+}
+
+// Sums of the segments' partials, element by element, into segment 0 (in place: a block reads
+// and writes its own 64 columns only).  16 threads of a column take every 16th segment, their
+// sums are added in order.  k_gram_reduce alone walked the segments one after the other in
+// each of its M1 nb^2 threads: 447 us for 768 segments at m_max = 16.
+__global__ __launch_bounds__(1024) void k_segment_sum(double *part, int64_t nseg, int64_t columns)
+{
+    __shared__ double sh[16][64];
+    const int e = threadIdx.x & 63, g = threadIdx.x >> 6;
+    double *col = part + (int64_t)blockIdx.x * 64 + e;
+    double acc = 0.0;
+#pragma unroll 8
+    for (int64_t s = g; s < nseg; s += 16) acc += col[s * columns];
+    sh[g][e] = acc;
+    __syncthreads();
+    if (g == 0) {
+#pragma unroll
+        for (int k = 1; k < 16; ++k) acc += sh[k][e];
+        col[0] = acc;
+    }
+}
+
+// Segments up to which the final reduction takes them itself (one launch less).
+constexpr int64_t kDirectSegments = 8;
+
+static z3_status sum_segments(double *part, int64_t *nseg, int64_t columns, hipStream_t s)
+{
+    if (*nseg <= kDirectSegments) return Z3_OK;
+    hipLaunchKernelGGL(k_segment_sum, dim3((unsigned)(columns / 64)), dim3(1024), 0, s, part, *nseg, columns);
+    *nseg = 1;
+    return check_launch("k_segment_sum");
 }
 
 // G(u, v) of one segment, read from the tile holding min/max of (u, v).
@@ -65,17 +120,11 @@ __global__ void k_gram_reduce(const double *part, int64_t nseg, int nmaps, int M
     z[1] += ir - ri;
 }
 
-// ---- LDS-staged pair contraction over pivot-minor multipoles --------------------------------
+// ---- pair contraction over pivot-minor multipoles -------------------------------------------
 // G = sum_p v_p U1_p U2_p^T per (map, m): with U1 = U2 the Gram matrix of one field (only the
 // tile pairs on or above the diagonal), else the full product of two fields (the multi-field
 // estimator: Re zeta_m(b1, b2) = G(r1, r2) + G(i1, i2), Im zeta_m(b1, b2) = G(i1, r2) -
-// G(r1, i2), i.e. sum_p v_p X1(b1) conj(X2(b2))).  One block per (pivot segment, map, m):
-// tiles of kCrossKP pivots of the fields' 2nb rows of that m are staged in LDS as
-// [pivot][row], consecutive pivots of a row on consecutive lanes (one contiguous run of the
-// pivot-minor layout), and the waves run the 16 x 16 tile pairs out of LDS, so every
-// multipole is read from memory once per launch; the next tile's loads are in flight
-// during the current tile's MFMAs.  MFMA as in the pivot-major contraction below (split FP32
-// operand on the mixed path), fixed-order FP64 sums.
+// G(r1, i2), i.e. sum_p v_p X1(b1) conj(X2(b2))).
 
 struct PairArgs {
     const void *A1, *A2;  // [map][m+1][2][nb][ldA] multipoles of the b1 and b2 fields (Gram: A1 only)
@@ -85,29 +134,193 @@ struct PairArgs {
     size_t a_stride;      // elements between the maps' multipoles (Gram of several maps)
     size_t v_stride;      // elements between the maps' pivot products
     int nb, T, M1, nmaps;
+    int seg;              // pivots per segment
     int npairs;           // tile pairs per (map, m): T^2, or T (T + 1) / 2 for a Gram matrix
-    int ldr;              // LDS row length: the least >= 2 nb that is 17 mod 32 (conflict-free
-                          // staging writes, 16 pivots of a row 17 banks apart; operand reads
-                          // of the four pivot groups nearly so)
+    int ldr;              // k_pair_lds: LDS row length
     double *part;         // [seg][map][m][npairs][256]
 };
 
-constexpr int kCrossKP = 32;  // pivots per LDS tile of the multi-field contraction (8 MFMA k-steps)
+// k_pair, the mixed path up to T = 4 row tiles (T = 3 for the product of two fields): one block
+// of four waves per (segment, map, m).  A wave takes every fourth group of 16 pivots and forms
+// all tile pairs of it: lane (row r, quarter q) loads 4 consecutive pivots of row r of each row
+// tile, the next group's loads in flight during the current group's MFMAs.  An operand is read
+// and split once for all the tile pairs that take it, nothing goes through LDS and the waves
+// meet only once, to add their sums in wave order.  The FP32 sums run over the pivots of a
+// group in increasing order, four per MFMA (step s takes the pivots 4 s + q): the lanes'
+// quadruples are transposed between the four quarters of the wave.
+// At 20 bins, m_max = 10 and 6.3e6 pivots (5.5 GB) 5.9 ms, against 7.5 ms for tiles of pivots in
+// LDS with one wave per tile pair.  Bound by issue: per group 48 MFMAs of 32 cycles (47% of the
+// time) and the splits' conversions, which do not overlap them (counters).  On the FP64 path,
+// without splits, the same form is slower than the LDS tiles (2.87 against 2.58 ms at 15 bins,
+// m_max = 16, 12.8 GB: both near the copy rate).
+typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));  // rows start anywhere
 
-// NW waves per block, UPW tile pairs per wave, tile pairs blockIdx.y NW UPW onwards; each
-// thread stages up to ROWS rows of both fields per tile (2 nb <= 16 T <= ROWS x 2 NW for
-// every shape launched).  SYM: a Gram matrix of one field (A2 = A1; only the tile pairs on
-// or above the diagonal, the others are their mirror).
-template <bool F32, int NW, int UPW, int ROWS, bool SYM>
+// x[i] of quarter q = element 4 q + i  ->  x[s] of quarter q = element 4 s + q
+__device__ __forceinline__ void transpose_quarters(float (&x)[4])
+{
+    auto swap16 = [](float &a, float &b) {
+        auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        a = __uint_as_float(r[0]);
+        b = __uint_as_float(r[1]);
+    };
+    auto swap32 = [](float &a, float &b) {
+        auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        a = __uint_as_float(r[0]);
+        b = __uint_as_float(r[1]);
+    };
+    swap16(x[0], x[1]);
+    swap16(x[2], x[3]);
+    swap32(x[0], x[2]);
+    swap32(x[1], x[3]);
+}
+
+constexpr int kPairWaves = 4;
+
+template <int T, bool SYM>
+__global__ __launch_bounds__(kPairWaves * 64) void k_pair(PairArgs c)
+{
+    constexpr int NP = SYM ? T * (T + 1) / 2 : T * T;
+    __shared__ double sums[kPairWaves][256];
+    const int64_t unit = blockIdx.x;  // (segment, map, m)
+    const int m = (int)(unit % c.M1);
+    const int map = (int)((unit / c.M1) % c.nmaps);
+    const int64_t seg = unit / ((int64_t)c.M1 * c.nmaps);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row = lane & 15, q = lane >> 4;
+    const int rows = 2 * c.nb;
+    const size_t mo = (size_t)map * c.a_stride + (size_t)2 * m * c.nb * c.ldA;
+    const double *v = c.v + (size_t)map * c.v_stride;
+    const int64_t pbeg = seg * c.seg;
+    const int64_t pend = min(c.npiv, pbeg + c.seg);
+
+    // this lane's rows, one per row tile; a padding row reads row 0 and counts as zeros
+    const float *src1[T], *src2[T];
+    bool in[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const int u = 16 * t + row;
+        in[t] = u < rows;
+        const size_t o = mo + (in[t] ? (size_t)u * c.ldA : 0);
+        src1[t] = static_cast<const float *>(c.A1) + o;
+        src2[t] = static_cast<const float *>(SYM ? c.A1 : c.A2) + o;
+    }
+    // this quarter's four pivots of group g: one load, or only those below pend
+    auto load4 = [&](const float *s, int64_t g, bool whole, bool rin, float (&x)[4]) __attribute__((always_inline)) {
+        const int64_t p = g + 4 * q;
+        if (whole) {
+            const f4_any r = *reinterpret_cast<const f4_any *>(s + p);
+            x[0] = r.x; x[1] = r.y; x[2] = r.z; x[3] = r.w;
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i] = p + i < pend ? s[p + i] : 0.0f;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = rin ? x[i] : 0.0f;
+    };
+    float x1[T][4], x2[SYM ? 1 : T][4];
+    double vk[4];
+    auto fetch = [&](int64_t g) __attribute__((always_inline)) {
+        const bool whole = g + 16 <= pend;  // wave-uniform
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            load4(src1[t], g, whole, in[t], x1[t]);
+            if constexpr (!SYM) load4(src2[t], g, whole, in[t], x2[SYM ? 0 : t]);
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int64_t p = g + 4 * s + q;
+            vk[s] = whole || p < pend ? v[p] : 0.0;
+        }
+    };
+    v4d acc[NP];
+#pragma unroll
+    for (int j = 0; j < NP; ++j) acc[j] = v4d{0.0, 0.0, 0.0, 0.0};
+    int64_t g = pbeg + 16 * wave;
+    if (g < pend) fetch(g);
+    for (; g < pend; g += 16 * kPairWaves) {
+        // operands: the scaled rows of field 1 as hi + lo, the rows of field 2
+        float hi[T][4], lo[T][4], b[T][4];
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) b[t][i] = SYM ? x1[t][i] : x2[SYM ? 0 : t][i];
+            if constexpr (!SYM) transpose_quarters(x1[t]);
+            transpose_quarters(b[t]);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const double av = (double)(SYM ? b[t][s] : x1[t][s]) * vk[s];
+                hi[t][s] = (float)av;
+                lo[t][s] = (float)(av - (double)hi[t][s]);
+            }
+        }
+        const int64_t gn = g + 16 * kPairWaves;
+        if (gn < pend) fetch(gn);
+        // FP32 products over 16 pivots, then into the FP64 sums
+        v4f part[NP];
+#pragma unroll
+        for (int j = 0; j < NP; ++j) part[j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+#pragma unroll
+            for (int I = 0, j = 0; I < T; ++I)
+#pragma unroll
+                for (int J = SYM ? I : 0; J < T; ++J, ++j)
+                    part[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(hi[I][s], b[J][s], part[j], 0, 0, 0);
+#pragma unroll
+            for (int I = 0, j = 0; I < T; ++I)
+#pragma unroll
+                for (int J = SYM ? I : 0; J < T; ++J, ++j)
+                    part[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(lo[I][s], b[J][s], part[j], 0, 0, 0);
+        }
+#pragma unroll
+        for (int j = 0; j < NP; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[j][r] += (double)part[j][r];
+    }
+    double *out = c.part + (size_t)unit * (size_t)NP * 256;
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+        if (j) __syncthreads();
+        // f32 16x16x4 result: register r of lane l is D[4 (l/16) + r][l % 16]
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sums[wave][(4 * q + r) * 16 + row] = acc[j][r];
+        __syncthreads();
+        double s = sums[0][tid];
+#pragma unroll
+        for (int w = 1; w < kPairWaves; ++w) s += sums[w][tid];
+        out[(size_t)j * 256 + tid] = s;
+    }
+}
+
+// k_pair_lds: one block per (segment, map, m) (and 16 tile pairs beyond T = 4).  Tiles of KP
+// pivots of the fields' 2nb rows of that m are staged in LDS as [pivot][row], consecutive
+// pivots of a row on consecutive lanes (one contiguous run of the pivot-minor layout), and the
+// waves run the 16 x 16 tile pairs out of LDS, so every multipole is read from memory once per
+// launch; the next tile's loads are in flight during the current tile's MFMAs.  The scaled
+// operand v_p U1 is formed once per element when it is staged (on the mixed path as hi + lo),
+// not once per tile pair that reads it.  The LDS row length is the least >= 2 nb that is 17 mod
+// 32 (conflict-free staging writes, 16 pivots of a row 17 banks apart; operand reads of the
+// four pivot groups nearly so).  Fixed-order FP64 sums.
+//
+// Pivots per tile: 32, but 16 for the Gram matrix of more than 64 FP64 rows, whose two tiles
+// would otherwise take 74 KB of LDS (the two fields' product takes that).
+constexpr int pair_kp(bool f32, bool sym, int T) { return !f32 && sym && T > 4 ? 16 : 32; }
+
+// NW waves per block, one tile pair per wave, tile pairs blockIdx.y NW onwards; each thread
+// stages up to ROWS rows of both fields per tile (2 nb <= 16 T <= ROWS x (64 NW / KP) for every
+// shape launched).  SYM: a Gram matrix of one field (A2 = A1; only the tile pairs on or above
+// the diagonal, the others are their mirror).
+template <bool F32, int NW, int KP, int ROWS, bool SYM>
 __global__ __launch_bounds__(NW * 64) void k_pair_lds(PairArgs c)
 {
     typedef typename std::conditional<F32, float, double>::type E;
-    constexpr int kThreads = NW * 64, kRows = ROWS;
+    constexpr int kThreads = NW * 64;
     extern __shared__ __align__(16) unsigned char smem[];
     const int ldr = c.ldr;
-    E *t1 = reinterpret_cast<E *>(smem);                          // [kCrossKP][ldr]
-    E *t2 = SYM ? t1 : t1 + kCrossKP * ldr;                       // [kCrossKP][ldr]
-    double *vt = reinterpret_cast<double *>(t1 + (SYM ? 1 : 2) * kCrossKP * ldr);  // [kCrossKP]
+    E *ta = reinterpret_cast<E *>(smem);  // [KP][ldr] v_p U1 (mixed: its hi part)
+    E *tb = ta + KP * ldr;                // [KP][ldr] U2
+    E *tl = tb + KP * ldr;                // [KP][ldr] mixed: the lo part of v_p U1
     const int64_t unit = blockIdx.x;  // (segment, map, m)
     const int m = (int)(unit % c.M1);
     const int map = (int)((unit / c.M1) % c.nmaps);
@@ -120,36 +333,34 @@ __global__ __launch_bounds__(NW * 64) void k_pair_lds(PairArgs c)
     const E *src2 = static_cast<const E *>(SYM ? c.A1 : c.A2) + mo;
     const double *v = c.v + (size_t)map * c.v_stride;
 
-    int ua[UPW], ub[UPW];
-    v4d acc[UPW];
-#pragma unroll
-    for (int j = 0; j < UPW; ++j) {
-        const int tp = (int)blockIdx.y * NW * UPW + wave + NW * j;
-        acc[j] = v4d{0.0, 0.0, 0.0, 0.0};
-        ua[j] = ub[j] = -1;
-        if (tp < c.npairs) {
-            int I = tp / T, J = tp % T;
-            if constexpr (SYM) {
-                int r = tp;
-                I = 0;
-                while (r >= T - I) { r -= T - I; ++I; }
-                J = I + r;
-            }
-            ua[j] = I * 16 + row;
-            ub[j] = J * 16 + row;
+    const int tp = (int)blockIdx.y * NW + wave;
+    int ua = -1, ub = -1;
+    v4d acc = {0.0, 0.0, 0.0, 0.0};
+    if (tp < c.npairs) {
+        int I = tp / T, J = tp % T;
+        if constexpr (SYM) {
+            int r = tp;
+            I = 0;
+            while (r >= T - I) { r -= T - I; ++I; }
+            J = I + r;
         }
+        ua = I * 16 + row;
+        ub = J * 16 + row;
     }
-    const int64_t pbeg = seg * kSeg;
-    const int64_t pend = min(c.npiv, pbeg + kSeg);
-    // staging: thread -> (row u, pivot k), kCrossKP pivots of a row on consecutive lanes (one
-    // contiguous run of the pivot-minor layout); the next tile's global loads are issued
-    // before the current tile's MFMAs
-    const int k = tid % kCrossKP, u0 = tid / kCrossKP, ustep = kThreads / kCrossKP;
-    E a[kRows], b[kRows];
+    const bool in_a = ua >= 0 && ua < two_nb, in_b = ub >= 0 && ub < two_nb;
+    const int64_t pbeg = seg * c.seg;
+    const int64_t pend = min(c.npiv, pbeg + c.seg);
+    // staging: thread -> (row u, pivot k), KP pivots of a row on consecutive lanes; the next
+    // tile's global loads are issued before the current tile's MFMAs
+    const int k = tid % KP, u0 = tid / KP;
+    constexpr int ustep = kThreads / KP;
+    E a[ROWS], b[SYM ? 1 : ROWS];
+    double vk = 0.0;
     auto fetch = [&](int64_t q0) {
         const bool kin = q0 + k < pend;
+        vk = kin ? v[q0 + k] : 0.0;
 #pragma unroll
-        for (int i = 0; i < kRows; ++i) {
+        for (int i = 0; i < ROWS; ++i) {
             const int uu = u0 + i * ustep;
             const bool in = uu < two_nb && kin;
             a[i] = in ? src1[(size_t)uu * c.ldA + q0 + k] : E(0);
@@ -157,96 +368,80 @@ __global__ __launch_bounds__(NW * 64) void k_pair_lds(PairArgs c)
         }
     };
     fetch(pbeg);
-    for (int64_t p0 = pbeg; p0 < pend; p0 += kCrossKP) {
-        const int np = (int)min((int64_t)kCrossKP, pend - p0);
+    for (int64_t p0 = pbeg; p0 < pend; p0 += KP) {
         __syncthreads();  // the previous tile is consumed
 #pragma unroll
-        for (int i = 0; i < kRows; ++i) {
+        for (int i = 0; i < ROWS; ++i) {
             const int uu = u0 + i * ustep;
             if (uu < two_nb) {
-                t1[k * ldr + uu] = a[i];
-                if constexpr (!SYM) t2[k * ldr + uu] = b[i];
+                const double av = (double)a[i] * vk;
+                const E hi = (E)av;
+                ta[k * ldr + uu] = hi;
+                if constexpr (F32) tl[k * ldr + uu] = (float)(av - (double)hi);
+                tb[k * ldr + uu] = SYM ? a[i] : b[SYM ? 0 : i];
             }
         }
-        if (tid < kCrossKP) vt[tid] = tid < np ? v[p0 + tid] : 0.0;
         __syncthreads();
-        if (p0 + kCrossKP < pend) fetch(p0 + kCrossKP);
+        if (p0 + KP < pend) fetch(p0 + KP);
+        if (ua < 0) continue;  // wave-uniform
 #pragma unroll
-        for (int h = 0; h < kCrossKP / 16; ++h) {
-            double vk[4];
+        for (int h = 0; h < KP / 16; ++h) {
+            if constexpr (F32) {
+                // FP32 products over 16 pivots, then into the FP64 sum
+                v4f part = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) vk[ks] = vt[16 * h + 4 * ks + kq];
+                for (int ks = 0; ks < 4; ++ks) {
+                    const int base = (16 * h + 4 * ks + kq) * ldr;
+                    const float ahi = in_a ? ta[base + ua] : 0.0f;
+                    const float alo = in_a ? tl[base + ua] : 0.0f;
+                    const float x2 = in_b ? tb[base + ub] : 0.0f;
+                    part = __builtin_amdgcn_mfma_f32_16x16x4f32(ahi, x2, part, 0, 0, 0);
+                    part = __builtin_amdgcn_mfma_f32_16x16x4f32(alo, x2, part, 0, 0, 0);
+                }
 #pragma unroll
-            for (int j = 0; j < UPW; ++j) {
-                if (ua[j] < 0) continue;  // wave-uniform
-                if constexpr (F32) {
-                    // FP32 products over 16 pivots, then into the FP64 sum; the scaled operand
-                    // v_p U1 is formed in FP64 and carried as FP32 hi + lo
-                    v4f part = {0.0f, 0.0f, 0.0f, 0.0f};
+                for (int q = 0; q < 4; ++q) acc[q] += (double)part[q];
+            } else {
 #pragma unroll
-                    for (int ks = 0; ks < 4; ++ks) {
-                        const int base = (16 * h + 4 * ks + kq) * ldr;
-                        const float x1 = ua[j] < two_nb ? t1[base + ua[j]] : 0.0f;
-                        const float x2 = ub[j] < two_nb ? t2[base + ub[j]] : 0.0f;
-                        const double av = (double)x1 * vk[ks];
-                        const float ahi = (float)av;
-                        const float alo = (float)(av - (double)ahi);
-                        part = __builtin_amdgcn_mfma_f32_16x16x4f32(ahi, x2, part, 0, 0, 0);
-                        part = __builtin_amdgcn_mfma_f32_16x16x4f32(alo, x2, part, 0, 0, 0);
-                    }
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) acc[j][q] += (double)part[q];
-                } else {
-#pragma unroll
-                    for (int ks = 0; ks < 4; ++ks) {
-                        const int base = (16 * h + 4 * ks + kq) * ldr;
-                        const double x1 = ua[j] < two_nb ? t1[base + ua[j]] : 0.0;
-                        const double x2 = ub[j] < two_nb ? t2[base + ub[j]] : 0.0;
-                        acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x1 * vk[ks], x2, acc[j], 0, 0, 0);
-                    }
+                for (int ks = 0; ks < 4; ++ks) {
+                    const int base = (16 * h + 4 * ks + kq) * ldr;
+                    const double x1 = in_a ? ta[base + ua] : 0.0;
+                    const double x2 = in_b ? tb[base + ub] : 0.0;
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x1, x2, acc, 0, 0, 0);
                 }
             }
         }
     }
+    if (ua < 0) return;
+    double *out = c.part + ((size_t)unit * (size_t)c.npairs + tp) * 256;
+    // f64 16x16x4 result: register q of lane l is D[4q + l/16][l % 16]; f32 as in k_pair
 #pragma unroll
-    for (int j = 0; j < UPW; ++j) {
-        if (ua[j] < 0) continue;
-        const int tp = (int)blockIdx.y * NW * UPW + wave + NW * j;
-        double *out = c.part + ((size_t)unit * (size_t)c.npairs + tp) * 256;
-        // f64 16x16x4 result: register q of lane l is D[4q + l/16][l % 16];
-        // f32 16x16x4 result: register q of lane l is D[4 (l/16) + q][l % 16]
-#pragma unroll
-        for (int q = 0; q < 4; ++q) out[(F32 ? 4 * kq + q : 4 * q + kq) * 16 + row] = acc[j][q];
-    }
+    for (int q = 0; q < 4; ++q) out[(F32 ? 4 * kq + q : 4 * q + kq) * 16 + row] = acc[q];
 }
 
-template <bool F32, int NW, int UPW, int ROWS, bool SYM>
+// NW waves, at most T row tiles
+template <bool F32, int NW, int T, bool SYM>
 static void launch_pair_lds(dim3 grid, size_t lds, const PairArgs &c, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_pair_lds<F32, NW, UPW, ROWS, SYM>), grid, dim3(NW * 64), lds, s, c);
+    constexpr int KP = pair_kp(F32, SYM, T), kAtOnce = NW * 64 / KP;  // rows staged at a time
+    hipLaunchKernelGGL((k_pair_lds<F32, NW, KP, (16 * T + kAtOnce - 1) / kAtOnce, SYM>), grid, dim3(NW * 64), lds, s, c);
 }
 
+// The kernel and its shape for c.T row tiles.
 template <bool F32, bool SYM>
-static void launch_pair_shape(dim3 grid, size_t lds, const PairArgs &c, hipStream_t s)
-{
-    // one tile pair per wave, as many waves as pairs up to T = 4 (6 or 9 waves at T = 3: 9
-    // stage the 48 rows three per thread); beyond, groups of 16 pairs in blocks of their own
-    // (grid.y), each staging the whole tile
-    const int T = c.T;
-    if (T <= 2) launch_pair_lds<F32, 4, 1, 4, SYM>(grid, lds, c, s);
-    else if (T == 3 && SYM) launch_pair_lds<F32, 6, 1, 4, SYM>(grid, lds, c, s);
-    else if (T == 3) launch_pair_lds<F32, 9, 1, 3, SYM>(grid, lds, c, s);
-    else if (T == 4 && SYM) launch_pair_lds<F32, 10, 1, 4, SYM>(grid, lds, c, s);
-    else launch_pair_lds<F32, 16, 1, 4, SYM>(dim3(grid.x, (unsigned)((c.npairs + 15) / 16)), lds, c, s);
-}
-
-// LDS-staged pair contraction over pivot-minor multipoles: one block per (segment, map, m)
-static z3_status launch_pair(const PairArgs &c0, bool f32, bool sym, int64_t nseg, hipStream_t s)
+static z3_status launch_pair_shape(dim3 grid, const PairArgs &c0, hipStream_t s)
 {
     PairArgs c = c0;
+    const int T = c.T;
+    if (F32 && T <= (SYM ? 4 : 3)) {
+        const dim3 block(kPairWaves * 64);
+        if (T == 1) hipLaunchKernelGGL((k_pair<1, SYM>), grid, block, 0, s, c);
+        else if (T == 2) hipLaunchKernelGGL((k_pair<2, SYM>), grid, block, 0, s, c);
+        else if (T == 3) hipLaunchKernelGGL((k_pair<3, SYM>), grid, block, 0, s, c);
+        else if constexpr (SYM) hipLaunchKernelGGL((k_pair<4, SYM>), grid, block, 0, s, c);
+        return check_launch("k_pair");
+    }
     c.ldr = 2 * c.nb + ((17 - 2 * c.nb) % 32 + 32) % 32;
-    const size_t tile = (size_t)kCrossKP * c.ldr * (f32 ? 4 : 8);
-    const size_t lds = (sym ? 1 : 2) * (tile + 7) / 8 * 8 + kCrossKP * sizeof(double);
+    const size_t lds = (size_t)pair_kp(F32, SYM, T) * c.ldr * (F32 ? 3 * sizeof(float) : 2 * sizeof(double));
     int dev = 0, lds_max = 0;
     z3_status st = check_hip(hipGetDevice(&dev), "hipGetDevice");
     if (st == Z3_OK)
@@ -255,13 +450,29 @@ static z3_status launch_pair(const PairArgs &c0, bool f32, bool sym, int64_t nse
     if (lds > (size_t)lds_max)
         return fail(Z3_ERR_UNSUPPORTED, "contraction of %d bins needs %zu bytes of LDS per block (%d)", c.nb, lds,
                     lds_max);
+    // one tile pair per wave, as many waves as pairs up to T = 4 (6 or 9 waves at T = 3); beyond,
+    // groups of 16 pairs in blocks of their own (grid.y), each staging the whole tile
+    const dim3 grid16(grid.x, (unsigned)((c.npairs + 15) / 16));
+    if constexpr (!F32) {
+        if (T <= 2) launch_pair_lds<F32, 4, 2, SYM>(grid, lds, c, s);
+        else if (T == 3) launch_pair_lds<F32, SYM ? 6 : 9, 3, SYM>(grid, lds, c, s);
+        else if (T == 4) launch_pair_lds<F32, SYM ? 10 : 16, 4, SYM>(SYM ? grid : grid16, lds, c, s);
+        else launch_pair_lds<F32, 16, 8, SYM>(grid16, lds, c, s);
+    } else {
+        launch_pair_lds<F32, 16, 8, SYM>(grid16, lds, c, s);
+    }
+    return check_launch("k_pair_lds");
+}
+
+// Pair contraction over pivot-minor multipoles: one block per (segment, map, m)
+static z3_status launch_pair(const PairArgs &c, bool f32, bool sym, int64_t nseg, hipStream_t s)
+{
     const int64_t nblk = nseg * c.nmaps * c.M1;
     if (nblk > (int64_t)(UINT32_MAX / 1024))
         return fail(Z3_ERR_OVERFLOW, "contraction of %lld pivot segments x %d maps", (long long)nseg, c.nmaps);
     const dim3 grid((unsigned)nblk);
-    if (f32) sym ? launch_pair_shape<true, true>(grid, lds, c, s) : launch_pair_shape<true, false>(grid, lds, c, s);
-    else sym ? launch_pair_shape<false, true>(grid, lds, c, s) : launch_pair_shape<false, false>(grid, lds, c, s);
-    return check_launch("k_pair_lds");
+    if (f32) return sym ? launch_pair_shape<true, true>(grid, c, s) : launch_pair_shape<true, false>(grid, c, s);
+    return sym ? launch_pair_shape<false, true>(grid, c, s) : launch_pair_shape<false, false>(grid, c, s);
 }
 
 // ---- LDS-staged contraction of the pivot-major staging ------------------------------------
@@ -310,6 +521,7 @@ struct GramArgs {
     const double *v;
     size_t v_stride;
     int nb, R, T, ntp, M1, nmaps, nunits;
+    int seg;             // pivots per segment
     int lpr_shift;       // PM staging: log2 of the lanes per (pivot, bin) run of R rows
     size_t tile_bytes;
     double *part;        // [seg][map][m][tile pair][256]
@@ -355,8 +567,8 @@ __global__ __launch_bounds__(kGramThreads) void k_gram_lds(GramArgs g)
         }
     }
 
-    const int64_t pbeg = seg * kSeg;
-    const int64_t pend = min(g.npiv, pbeg + kSeg);
+    const int64_t pbeg = seg * g.seg;
+    const int64_t pend = min(g.npiv, pbeg + g.seg);
     for (int64_t p0 = pbeg; p0 < pend; p0 += kGramKP) {
         const int np = (int)min((int64_t)kGramKP, pend - p0);
         __syncthreads();  // the previous tile is consumed
@@ -451,8 +663,9 @@ static z3_status contract_src(int64_t npiv, int m_max, int nbins, int prec, int 
 {
     if (npiv <= 0 || nmaps <= 0) return Z3_OK;
     const int T = tiles_for(nbins), ntp = T * (T + 1) / 2;
-    const int64_t nseg = (npiv + kSeg - 1) / kSeg;
-    if (contract_partial_bytes(npiv, m_max, nbins) * (size_t)nmaps > partial_bytes)
+    const int seg = segment_pivots(npiv, (int64_t)nmaps * (m_max + 1) * ntp);
+    int64_t nseg = (npiv + seg - 1) / seg;
+    if (contract_partial_bytes(npiv, m_max, nbins, nmaps) > partial_bytes)
         return fail(Z3_ERR_INVALID_ARG, "contraction workspace too small");
     if (nseg > 65535) return fail(Z3_ERR_OVERFLOW, "too many pivots for one contraction (%lld)", (long long)npiv);
     if ((int64_t)nmaps * (m_max + 1) > 65535) return fail(Z3_ERR_OVERFLOW, "too many maps for one contraction");
@@ -476,6 +689,7 @@ static z3_status contract_src(int64_t npiv, int m_max, int nbins, int prec, int 
         g.M1 = m_max + 1;
         g.nmaps = nmaps;
         g.nunits = (m_max + 1) * ntp;
+        g.seg = seg;
         g.lpr_shift = g.R <= 32 ? 5 : 6;
         g.tile_bytes = gram_tile_bytes(nbins, g.R, f32);
         g.part = static_cast<double *>(partials);
@@ -498,9 +712,12 @@ static z3_status contract_src(int64_t npiv, int m_max, int nbins, int prec, int 
         c.M1 = m_max + 1;
         c.nmaps = nmaps;
         c.npairs = ntp;
+        c.seg = seg;
         c.part = static_cast<double *>(partials);
         st = launch_pair(c, f32, true, nseg, s);
     }
+    if (st == Z3_OK)
+        st = sum_segments(static_cast<double *>(partials), &nseg, (int64_t)nmaps * (m_max + 1) * ntp * 256, s);
     if (st != Z3_OK) return st;
     const int total = nmaps * (m_max + 1) * nbins * nbins;
     hipLaunchKernelGGL(k_gram_reduce, dim3((total + 127) / 128), dim3(128), 0, s,
@@ -561,8 +778,7 @@ __global__ void k_cross_reduce(const double *part, int64_t nseg, int M1, int nb,
 size_t cross_partial_bytes(int64_t npiv, int m_max, int nbins)
 {
     const int T = tiles_for(nbins);
-    const int64_t nseg = (npiv + kSeg - 1) / kSeg;
-    return (size_t)(nseg > 0 ? nseg : 1) * (size_t)(m_max + 1) * (size_t)(T * T) * 256 * sizeof(double);
+    return most_partials(npiv, (int64_t)(m_max + 1) * T * T) * 256 * sizeof(double);
 }
 
 z3_status launch_contract_cross(int64_t npiv, int m_max, int nbins, int prec, const void *A1, const void *A2,
@@ -571,7 +787,8 @@ z3_status launch_contract_cross(int64_t npiv, int m_max, int nbins, int prec, co
 {
     if (npiv <= 0) return Z3_OK;
     const int T = tiles_for(nbins);
-    const int64_t nseg = (npiv + kSeg - 1) / kSeg;
+    const int seg = segment_pivots(npiv, (m_max + 1) * T * T);
+    int64_t nseg = (npiv + seg - 1) / seg;
     if (partial_bytes < cross_partial_bytes(npiv, m_max, nbins))
         return fail(Z3_ERR_INVALID_ARG, "multi-field contraction: partial buffer too small");
     PairArgs c = {};
@@ -585,8 +802,10 @@ z3_status launch_contract_cross(int64_t npiv, int m_max, int nbins, int prec, co
     c.M1 = m_max + 1;
     c.nmaps = 1;
     c.npairs = T * T;
+    c.seg = seg;
     c.part = static_cast<double *>(partials);
     z3_status st = launch_pair(c, prec == Z3_PREC_MIXED, false, nseg, s);
+    if (st == Z3_OK) st = sum_segments(static_cast<double *>(partials), &nseg, (int64_t)(m_max + 1) * T * T * 256, s);
     if (st != Z3_OK) return st;
     const int total = (m_max + 1) * nbins * nbins;
     hipLaunchKernelGGL(k_cross_reduce, dim3((total + 127) / 128), dim3(128), 0, s,
