@@ -548,13 +548,14 @@ z3_status build_index_impl(int64_t n, const double *xyz, const double *w, int nb
     double h = cell_size;
     double *d_range = nullptr;
     if ((st = dalloc(&d_range, 3, "alloc range")) != Z3_OK) return bail(st);
-    if (planar && h <= 0.0) {
+    double area = 1.0;
+    if (planar) {
         // the same 1.4 x mean spacing as on the sphere
-        double area = lx * ly;
+        area = lx * ly;
         if (!(area > 0.0)) area = std::max(lx, ly) * std::max(lx, ly) / (double)std::max<int64_t>(n, 1);
         if (!(area > 0.0)) area = 1.0;
-        h = Z3_BAND_HEIGHT_FACTOR * sqrt(area / (double)std::max<int64_t>(n, 1));
-    } else if (!planar) {
+        if (h <= 0.0) h = Z3_BAND_HEIGHT_FACTOR * sqrt(area / (double)std::max<int64_t>(n, 1));
+    } else {
         double rg[3] = {kPi, 0.0, 0.0};
         st = check_hip(hipMemcpyAsync(d_range, rg, sizeof(rg), hipMemcpyHostToDevice, s), "copy range");
         if (st == Z3_OK && n > 0) {
@@ -571,9 +572,9 @@ z3_status build_index_impl(int64_t n, const double *xyz, const double *w, int nb
                              "z3_build_index: positions are not unit vectors (max | |r|^2 - 1 | = %g, limit %g)", rg[2],
                              kMaxNormDev));
         }
+        area = 2.0 * kPi * (cos(std::min(rg[0], rg[1])) - cos(std::max(rg[0], rg[1])));
+        if (!(area > 0.0)) area = 1e-12;
         if (h <= 0.0) {
-            double area = 2.0 * kPi * (cos(std::min(rg[0], rg[1])) - cos(std::max(rg[0], rg[1])));
-            if (!(area > 0.0)) area = 1e-12;
             // 1.4 x the mean point spacing: about two HEALPix rings per band (ring spacing
             // 2 / (3 Nside) rad at low latitudes, mean spacing ~1.023 / Nside).  Each band
             // costs every pivot one longitude window per bin, whose set-up (window bounds,
@@ -584,6 +585,7 @@ z3_status build_index_impl(int64_t n, const double *xyz, const double *w, int nb
         }
     }
     (void)hipFree(d_range);
+    idx->density = (double)n / area;
     int nbands = 1;
     if (planar) {
         const double nb_d = std::floor(ly / h) + 1.0;

@@ -57,6 +57,7 @@ struct z3_index_s {
     int64_t n = 0;
     int nbins = 0;
     double band_h = 0.0;
+    double density = 0.0;             // points per unit area of the colatitude range (plane: of the bounding box)
     int nbands = 0;
     int64_t ncells = 0;
     z3::EdgeTab edges{};
