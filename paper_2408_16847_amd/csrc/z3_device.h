@@ -67,6 +67,15 @@ __device__ __forceinline__ double load_f64(__amdgpu_buffer_rsrc_t v, uint32_t of
     return __builtin_bit_cast(double, (uint64_t)a.x | (uint64_t)a.y << 32);
 }
 
+// Two FP64 values at byte offset `off` of a buffer view (zeros past its range).
+__device__ __forceinline__ double2 load_f64x2(__amdgpu_buffer_rsrc_t v, uint32_t off)
+{
+    typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+    const u4 a = __builtin_amdgcn_raw_buffer_load_b128(v, off, 0, 0);
+    return make_double2(__builtin_bit_cast(double, (uint64_t)a.x | (uint64_t)a.y << 32),
+                        __builtin_bit_cast(double, (uint64_t)a.z | (uint64_t)a.w << 32));
+}
+
 __device__ __forceinline__ double4 load_record(__amdgpu_buffer_rsrc_t v, uint32_t off)
 {
     typedef unsigned int u4 __attribute__((ext_vector_type(4)));

@@ -176,6 +176,61 @@ constexpr int mult_waves_per_eu()
 constexpr int kWinBands = 8;
 constexpr uint32_t kNoRecord = 0xffffffe0u;  // past any band's records (a multiple of 64 B below 2^32)
 
+// Lists this lane's windows of the bands from k on, at most kWinBands of them (fewer when their
+// records span 2^32 bytes) and up to khi: byte ranges of the doubled records from record `base`
+// on, ended by kNoRecord.  Moves k past the bands listed; returns the bytes they span (every
+// byte offset of the list lies below).  `window(band, s0, l0, s1, l1)` gives a band's windows.
+template <class Window>
+__device__ __forceinline__ uint32_t list_windows(const Band *bands, int &k, int khi, uint2 *list, int &base,
+                                                 Window window)
+{
+    base = 2 * bands[k].pt_start;
+    uint32_t span = 0;
+    const int kend = min(khi + 1, k + kWinBands);
+    for (; k < kend; ++k) {
+        const Band bd = bands[k];
+        if (bd.npts == 0) continue;
+        // one band's records span less than 2^32 bytes (checked when the index is built)
+        const uint64_t reach = (uint64_t)(2 * (int64_t)(bd.pt_start + bd.npts) - base) * 32u;
+        if (reach > UINT32_MAX) break;
+        span = (uint32_t)reach;
+        int s0, l0, s1, l1;
+        window(bd, s0, l0, s1, l1);
+        const uint32_t first = (uint32_t)(2 * bd.pt_start - base);
+        if (l0 > 0) {
+            *list = make_uint2((first + s0) * 32u, (first + s0 + l0) * 32u);
+            list += kWave;
+        }
+        if (l1 > 0) {
+            *list = make_uint2((first + s1) * 32u, (first + s1 + l1) * 32u);
+            list += kWave;
+        }
+    }
+    *list = make_uint2(kNoRecord, kNoRecord);
+    return span;
+}
+
+// The records of a list of windows, one after the other; kNoRecord after the last.
+struct ListWalk {
+    const uint2 *at;
+    uint32_t end;
+    __device__ __forceinline__ explicit ListWalk(const uint2 *list) : at(list), end(0) {}
+    __device__ __forceinline__ uint32_t first() { return window(); }
+    __device__ __forceinline__ uint32_t next(uint32_t o)
+    {
+        o += 32u;
+        if (o >= end) o = window();
+        return o;
+    }
+    __device__ __forceinline__ uint32_t window()
+    {
+        const uint2 w = *at;
+        at += kWave;
+        end = w.y;
+        return w.x;
+    }
+};
+
 template <int M, bool F32OUT, bool IDS, bool SELF, bool PLANAR, bool LIST>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(mult_waves_per_eu<M>())))
 void k_multipoles(MultArgs a)
@@ -314,36 +369,14 @@ void k_multipoles(MultArgs a)
         };
         if constexpr (LIST) {
             for (int k = klo; k <= khi;) {
-                // the windows of the next kWinBands bands, as byte ranges of the doubled records from
-                // the first band's on, a list per lane that ends with kNoRecord
-                const int base = 2 * a.bands[k].pt_start;
-                uint32_t span = 0;
-                uint2 *wp = list;
-                const int kend = min(khi + 1, k + kWinBands);
-                for (; k < kend; ++k) {
-                    const Band bd = a.bands[k];
-                    if (bd.npts == 0) continue;
-                    // byte offsets stay below 2^32: one band does (checked when the index is
-                    // built), more bands are left to the next list otherwise
-                    const uint64_t reach = (uint64_t)(2 * (int64_t)(bd.pt_start + bd.npts) - base) * 32u;
-                    if (reach > UINT32_MAX) break;
-                    span = (uint32_t)reach;
-                    int s0, l0, s1, l1;
-                    if constexpr (PLANAR)
-                        planar_window(bd, a.cell_start, th, phd, a.psx, hav_out, hav_in, s0, l0, s1, l1);
-                    else
-                        band_window(bd, a.cell_start, th, sh, ch, inv_sp, phf, hav_out, hav_in, s0, l0, s1, l1);
-                    const uint32_t first = (uint32_t)(2 * bd.pt_start - base);
-                    if (l0 > 0) {
-                        *wp = make_uint2((first + s0) * 32u, (first + s0 + l0) * 32u);
-                        wp += kWave;
-                    }
-                    if (l1 > 0) {
-                        *wp = make_uint2((first + s1) * 32u, (first + s1 + l1) * 32u);
-                        wp += kWave;
-                    }
-                }
-                *wp = make_uint2(kNoRecord, kNoRecord);
+                int base;
+                const uint32_t span = list_windows(
+                    a.bands, k, khi, list, base, [&](const Band &bd, int &s0, int &l0, int &s1, int &l1) {
+                        if constexpr (PLANAR)
+                            planar_window(bd, a.cell_start, th, phd, a.psx, hav_out, hav_in, s0, l0, s1, l1);
+                        else
+                            band_window(bd, a.cell_start, th, sh, ch, inv_sp, phf, hav_out, hav_in, s0, l0, s1, l1);
+                    });
                 // their doubled records (wave-uniform base), walked by byte offset, and doubled
                 // weights (8 B per record: byte offset = record offset / 4)
                 const __amdgpu_buffer_rsrc_t rband = buffer_view(a.rec + base, span);
@@ -352,26 +385,16 @@ void k_multipoles(MultArgs a)
                 // or HBM miss overlaps the previous candidate's work; two candidates per trip with
                 // two record registers in turn, so the record requested ahead needs no copy.  A
                 // request at kNoRecord lies past the buffer's range and reads nothing.
-                const uint2 *wq = list + kWave;
-                uint32_t off = list->x, oend = list->y;
-                auto next = [&](uint32_t o) __attribute__((always_inline)) {
-                    o += 32u;
-                    if (o >= oend) {
-                        const uint2 w = *wq;
-                        o = w.x;
-                        oend = w.y;
-                        wq += kWave;
-                    }
-                    return o;
-                };
-                double4 ra = load_record(rband, off);
-                while (off != kNoRecord) {
-                    const uint32_t ob = next(off);
+                ListWalk walk(list);
+                uint32_t oa = walk.first();
+                double4 ra = load_record(rband, oa);
+                while (oa != kNoRecord) {
+                    const uint32_t ob = walk.next(oa);
                     const double4 rb = load_record(rband, ob);
-                    cand(ra, off, base, wband);
+                    cand(ra, oa, base, wband);
                     if (ob == kNoRecord) break;
-                    off = next(ob);
-                    ra = load_record(rband, off);
+                    oa = walk.next(ob);
+                    ra = load_record(rband, oa);
                     cand(rb, ob, base, wband);
                 }
             }
@@ -456,6 +479,9 @@ void k_multipoles(MultArgs a)
         if ((threadIdx.x & (kWave - 1)) == 0 && tot) atomicAdd((unsigned long long *)a.pair_total, (unsigned long long)tot);
     }
 }
+
+// Whether a launch over this index walks window lists (z3_multipoles.hip).
+bool short_windows(const z3_index_s *idx);
 
 // Launch over window lists (z3_multipoles_list.hip).
 z3_status launch_multipoles_list(int m_max, bool planar, bool mixed, bool self, const MultArgs &a, hipStream_t s);

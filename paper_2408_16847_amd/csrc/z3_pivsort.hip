@@ -75,7 +75,7 @@ z3_status sort_pivots(const z3_index_s *idx, Pivots piv, int64_t p0, int64_t len
     uint32_t *k_in = static_cast<uint32_t *>(wk), *k_out = k_in + n;
     int *v_in = reinterpret_cast<int *>(k_out + n);
     size_t tbytes = 0;
-    st = check_hip(rocprim::radix_sort_pairs(nullptr, tbytes, k_in, k_out, v_in, perm, n, 0, 32, s),
+    st = check_hip(rocprim::radix_sort_pairs(nullptr, tbytes, k_in, k_out, v_in, perm, n, 0, bits + fb, s),
                    "pivot sort size");
     // a non-null temporary buffer: a null one only asks for its size
     if (st == Z3_OK) st = scratch_alloc(&wt, tbytes > 256 ? tbytes : 256, s);
@@ -86,7 +86,7 @@ z3_status sort_pivots(const z3_index_s *idx, Pivots piv, int64_t p0, int64_t len
         st = check_launch("k_pivot_keys");
     }
     if (st == Z3_OK)
-        st = check_hip(rocprim::radix_sort_pairs(wt, tbytes, k_in, k_out, v_in, perm, n, 0, 32, s), "pivot sort");
+        st = check_hip(rocprim::radix_sort_pairs(wt, tbytes, k_in, k_out, v_in, perm, n, 0, bits + fb, s), "pivot sort");
     scratch_free(wt, s);
     scratch_free(wk, s);
     return st;
