@@ -108,7 +108,8 @@ z3_status z3_build_index(int64_t n, const double *xyz, const double *w, int nbin
  * Attach field values: nmaps maps of n values each, x [nmaps][n] FP64 in the
  * catalogue's original order.  The index stores w_i x_i in index order and, per map,
  * 32-byte neighbour records {x, y, z, w x} (2 n records: every latitude band is stored
- * twice in a row).  Waits for earlier work on `stream`; replaces values attached before.
+ * twice in a row).  Replaces values attached before, and then waits for the device's earlier
+ * work, which may still read them.
  */
 z3_status z3_index_set_values(z3_index idx, int nmaps, const double *x, void *stream);
 
@@ -185,7 +186,11 @@ z3_status z3_build_index_planar(int64_t n, const double *xy, const double *w, in
                                 const double *edges_d2, double cell_size, void *stream,
                                 z3_index *out);
 
-/* Release an index and its device memory (NULL is ignored).  Waits for its work. */
+/*
+ * Release an index and its device memory (NULL is ignored).  Waits for the device's work.  The
+ * library keeps up to 4 GiB of such memory per device for the next index; it gives it back
+ * when an allocation of its own fails.
+ */
 void z3_index_free(z3_index idx);
 
 /*

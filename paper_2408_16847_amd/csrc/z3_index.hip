@@ -10,8 +10,7 @@
 // the index and every later sum deterministic.
 #include <algorithm>
 #include <cmath>
-#include <cstring>
-#include <vector>
+#include <new>
 
 #include "z3_internal.h"
 
@@ -83,54 +82,215 @@ __global__ __launch_bounds__(256) void k_sky_range(const double *xyz, int64_t n,
     }
 }
 
-// colatitude ranges of the bands start empty: [lo0, 0]
-__global__ void k_init_band_th(double *band_th, int nbands, double lo0)
+// Start of a build: the edge table (by value, so that it needs no copy from the host) and the
+// empty range of k_sky_range.
+__global__ void k_index_begin(EdgeTab e, EdgeTab *edges, double *range)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nbands) return;
-    band_th[2 * k] = lo0;
-    band_th[2 * k + 1] = 0.0;
+    const double *src = reinterpret_cast<const double *>(&e);
+    double *dst = reinterpret_cast<double *>(edges);
+    for (int i = threadIdx.x; i < (int)(sizeof(EdgeTab) / sizeof(double)); i += blockDim.x) dst[i] = src[i];
+    if (threadIdx.x == 0) { range[0] = kPi; range[1] = 0.0; range[2] = 0.0; }
 }
 
-__global__ void k_set_int(int *p, int v) { *p = v; }
+// No points in any band or cell; the bands' colatitude ranges start empty, [lo0, 0].
+__global__ void k_clear_counts(int *band_count, double *band_th, int nbands, double lo0, int *cell_count, int64_t cells)
+{
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cells || i < nbands;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        if (i < cells) cell_count[i] = 0;
+        if (i < nbands) {
+            band_count[i] = 0;
+            band_th[2 * i] = lo0;
+            band_th[2 * i + 1] = 0.0;
+        }
+    }
+}
 
-// Band of every point, with per-band counts and colatitude ranges.  Consecutive points
-// usually share a band, so the lanes of a wave combine their updates per distinct band
-// before touching global memory.
-__global__ void k_band_of_point(const double *xyz, int64_t n, double inv_h, int nbands, int *band,
-                                double *phi_out, int *band_count, double *band_th /* [nbands][2] */)
+// Adds one point per valid lane to its band's count and colatitude range, in LDS or in memory.
+// Points in a map's order share a band with most of their wave, which then sends one update for
+// them all; a catalogue in no spatial order has up to 64 bands in a wave, and beyond a small
+// group each lane sends its own.  The range's atomics are left out where the range read already
+// covers the point (a stale read only sends an atomic too many).
+__device__ __forceinline__ void add_to_bands(bool valid, int k, double th, double lo0, int *count, double *th_lo,
+                                             double *th_hi, int stride)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    uint64_t todo = __ballot(valid);
+    while (todo) {
+        const int leader = __ffsll((unsigned long long)todo) - 1;
+        const int kl = __shfl(k, leader, kWave);
+        const bool mine = (todo >> lane & 1) && k == kl;
+        const uint64_t grp = __ballot(mine);
+        if (__popcll(grp) < 16) break;
+        double lo = mine ? th : lo0, hi = mine ? th : 0.0;
+        for (int o = 32; o > 0; o >>= 1) {
+            lo = fmin(lo, __shfl_xor(lo, o, kWave));
+            hi = fmax(hi, __shfl_xor(hi, o, kWave));
+        }
+        if (lane == leader) {
+            atomicAdd(&count[kl], (int)__popcll(grp));
+            atomic_min_pos_double(&th_lo[(int64_t)kl * stride], lo);
+            atomic_max_pos_double(&th_hi[(int64_t)kl * stride], hi);
+        }
+        todo &= ~grp;
+    }
+    if (todo >> lane & 1) {
+        atomicAdd(&count[k], 1);
+        const volatile double *lo = th_lo + (int64_t)k * stride, *hi = th_hi + (int64_t)k * stride;
+        if (!(*lo <= th)) atomic_min_pos_double(&th_lo[(int64_t)k * stride], th);
+        if (!(*hi >= th)) atomic_max_pos_double(&th_hi[(int64_t)k * stride], th);
+    }
+}
+
+// A point's band and longitude, on the sky or on a plane (strip of y, cell coordinate of x).
+struct BandRule {
+    double inv_h, x0, y0, sx, lo0;  // plane: origin and scale; lo0: an empty band's lower bound
+    int nbands;
+};
+
+template <bool PLANE>
+__device__ __forceinline__ int band_of(const double *xyz, int64_t n, int64_t i, const BandRule &r, double &th, double &phi)
+{
+    const double x = xyz[i], y = xyz[n + i];
+    if constexpr (PLANE) {
+        th = y - r.y0;  // >= 0: y0 is the smallest y
+        phi = (x - r.x0) * r.sx;
+    } else {
+        th = colatitude(x, y, xyz[2 * n + i]);
+        phi = longitude(x, y);
+    }
+    const int k = (int)(th * r.inv_h);
+    return k < 0 ? 0 : (k >= r.nbands ? r.nbands - 1 : k);
+}
+
+// Band of every point, with per-band counts and colatitude ranges.
+template <bool PLANE>
+__global__ void k_band_of_point(const double *xyz, int64_t n, BandRule r, int *band, double *phi_out, int *band_count,
+                                double *band_th /* [nbands][2] */)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const bool valid = i < n;
     int k = -1;
     double th = 0.0;
     if (valid) {
-        const double x = xyz[i], y = xyz[n + i], z = xyz[2 * n + i];
-        th = colatitude(x, y, z);
-        k = (int)(th * inv_h);
-        k = k < 0 ? 0 : (k >= nbands ? nbands - 1 : k);
-        band[i] = k;
-        phi_out[i] = longitude(x, y);
+        double phi;
+        band[i] = k = band_of<PLANE>(xyz, n, i, r, th, phi);
+        phi_out[i] = phi;
     }
-    const int lane = threadIdx.x & (kWave - 1);
-    uint64_t todo = __ballot(valid);
-    while (todo) {
-        const int leader = __ffsll((unsigned long long)todo) - 1;
-        const int kl = __shfl(k, leader, kWave);
-        const bool mine = valid && k == kl;
-        const uint64_t grp = __ballot(mine);
-        double lo = mine ? th : 4.0, hi = mine ? th : 0.0;
-        for (int o = 32; o > 0; o >>= 1) {
-            lo = fmin(lo, __shfl_xor(lo, o, kWave));
-            hi = fmax(hi, __shfl_xor(hi, o, kWave));
-        }
-        if (lane == leader) {
-            atomicAdd(&band_count[kl], (int)__popcll(grp));
-            atomic_min_pos_double(&band_th[2 * kl], lo);
-            atomic_max_pos_double(&band_th[2 * kl + 1], hi);
-        }
-        todo &= ~grp;
+    add_to_bands(valid, k, th, r.lo0, band_count, band_th, band_th + 1, 2);
+}
+
+// The same for up to kLdsBands bands: a block of 1024 threads takes a contiguous run of `run`
+// points, counts in LDS and sends its totals once.  Points in random order otherwise update a
+// few hundred addresses from every lane (150,000 points of a cap: 355 us with one wave-wide
+// reduction per band of a wave, 201 us with an atomic per lane).
+constexpr int kLdsBands = 2048;
+constexpr int kLdsBandThreads = 1024;
+
+template <bool PLANE>
+__global__ __launch_bounds__(kLdsBandThreads) void k_band_of_point_lds(const double *xyz, int64_t n, int64_t run, BandRule r,
+                                                                       int *band, double *phi_out, int *band_count,
+                                                                       double *band_th)
+{
+    __shared__ int count[kLdsBands];
+    __shared__ double lo[kLdsBands], hi[kLdsBands];
+    for (int k = threadIdx.x; k < r.nbands; k += kLdsBandThreads) {
+        count[k] = 0;
+        lo[k] = r.lo0;
+        hi[k] = 0.0;
     }
+    __syncthreads();
+    const int64_t beg = (int64_t)blockIdx.x * run, end = min(n, beg + run);
+    for (int64_t i0 = beg; i0 < end; i0 += kLdsBandThreads) {
+        const int64_t i = i0 + threadIdx.x;
+        const bool valid = i < end;
+        int k = -1;
+        double th = 0.0;
+        if (valid) {
+            double phi;
+            band[i] = k = band_of<PLANE>(xyz, n, i, r, th, phi);
+            phi_out[i] = phi;
+        }
+        add_to_bands(valid, k, th, r.lo0, count, lo, hi, 1);
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < r.nbands; k += kLdsBandThreads)
+        if (count[k]) {
+            atomicAdd(&band_count[k], count[k]);
+            atomic_min_pos_double(&band_th[2 * k], lo[k]);
+            atomic_max_pos_double(&band_th[2 * k + 1], hi[k]);
+        }
+}
+
+template <bool PLANE>
+static z3_status launch_band_of_point(const double *xyz, int64_t n, const BandRule &r, int *band, double *phi, int *count,
+                                      double *th, hipStream_t s)
+{
+    if (n <= 0) return Z3_OK;
+    if (r.nbands <= kLdsBands) {
+        const int64_t blocks = std::min<int64_t>((n + kLdsBandThreads - 1) / kLdsBandThreads, 512);
+        const int64_t run = ((n + blocks - 1) / blocks + kLdsBandThreads - 1) / kLdsBandThreads * kLdsBandThreads;
+        hipLaunchKernelGGL(k_band_of_point_lds<PLANE>, dim3((unsigned)((n + run - 1) / run)), dim3(kLdsBandThreads), 0, s, xyz,
+                           n, run, r, band, phi, count, th);
+    } else {
+        hipLaunchKernelGGL(k_band_of_point<PLANE>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, xyz, n, r, band, phi,
+                           count, th);
+    }
+    return check_launch("k_band_of_point");
+}
+
+// The band table from the counts and colatitude ranges, and [2]: number of cells, largest
+// count.  One block walks the bands 1024 at a time with running offsets.
+constexpr int kTableThreads = 1024;
+__global__ __launch_bounds__(kTableThreads) void k_band_table(int nbands, double h, const int *count, const double *band_th,
+                                                             Band *bands, int *stats)
+{
+    __shared__ int wpts[kTableThreads / kWave], wcells[kTableThreads / kWave], wmax[kTableThreads / kWave];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    int pt0 = 0, cell0 = 0, most = 0;  // of the bands before this round
+    for (int k0 = 0; k0 < nbands; k0 += kTableThreads) {
+        const int k = k0 + (int)threadIdx.x;
+        const int npts = k < nbands ? count[k] : 0;
+        const int ncell = k < nbands ? max(1, kCellsPerPoint * npts) : 0;
+        int p = npts, c = ncell, mx = npts;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int tp = __shfl_up(p, o, kWave), tc = __shfl_up(c, o, kWave);
+            if (lane >= o) { p += tp; c += tc; }
+            mx = max(mx, __shfl_xor(mx, o, kWave));
+        }
+        __syncthreads();  // the previous round's wave sums are read
+        if (lane == kWave - 1) { wpts[wave] = p; wcells[wave] = c; wmax[wave] = mx; }
+        __syncthreads();
+        int pb = pt0 + p - npts, cb = cell0 + c - ncell;
+        for (int w = 0; w < kTableThreads / kWave; ++w) {
+            if (w < wave) { pb += wpts[w]; cb += wcells[w]; }
+            pt0 += wpts[w];
+            cell0 += wcells[w];
+            most = max(most, wmax[w]);
+        }
+        if (k < nbands) {
+            Band b;
+            b.npts = npts;
+            b.pt_start = pb;
+            b.ncell = ncell;
+            b.cell_off = cb;
+            b.cells_per_rad = (float)((double)ncell / kTwoPi);
+            const double lo = npts ? band_th[2 * (int64_t)k] : k * h, hi = npts ? band_th[2 * (int64_t)k + 1] : k * h;
+            b.th_lo = lo;
+            b.th_hi = hi;
+            sincos(0.5 * lo, &b.sh_lo, &b.ch_lo);
+            sincos(0.5 * hi, &b.sh_hi, &b.ch_hi);
+            const double slo = sin(lo), shi = sin(hi);
+            const double smin = fmin(slo, shi);
+            const double smax = (lo <= 0.5 * kPi && hi >= 0.5 * kPi) ? 1.0 : fmax(slo, shi);
+            b.inv_smin = smin > 0.0 ? (float)(1.0 / smin) : INFINITY;
+            b.inv_smax = smax > 0.0 ? (float)(1.0 / smax) : INFINITY;
+            b.pad_ = 0;
+            bands[k] = b;
+        }
+    }
+    if (threadIdx.x == 0) { stats[0] = cell0; stats[1] = most; }
 }
 
 __global__ void k_cell_of_point(int64_t n, const int *band, const double *phi, const Band *bands,
@@ -185,49 +345,13 @@ __global__ void k_plane_xyz(const double *xy, int64_t n, double *xyz)
     xyz[2 * n + i] = 0.0;
 }
 
-// Strip of every point (y - y0 in place of the colatitude) and its cell coordinate.
-__global__ void k_band_of_point_plane(const double *xyz, int64_t n, double y0, double inv_h, double x0, double sx,
-                                      int nbands, int *band, double *phi_out, int *band_count,
-                                      double *band_th /* [nbands][2] */)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool valid = i < n;
-    int k = -1;
-    double th = 0.0;
-    if (valid) {
-        th = xyz[n + i] - y0;  // >= 0: y0 is the smallest y
-        k = (int)(th * inv_h);
-        k = k < 0 ? 0 : (k >= nbands ? nbands - 1 : k);
-        band[i] = k;
-        phi_out[i] = (xyz[i] - x0) * sx;
-    }
-    const int lane = threadIdx.x & (kWave - 1);
-    uint64_t todo = __ballot(valid);
-    while (todo) {
-        const int leader = __ffsll((unsigned long long)todo) - 1;
-        const int kl = __shfl(k, leader, kWave);
-        const bool mine = valid && k == kl;
-        const uint64_t grp = __ballot(mine);
-        double lo = mine ? th : INFINITY, hi = mine ? th : 0.0;
-        for (int o = 32; o > 0; o >>= 1) {
-            lo = fmin(lo, __shfl_xor(lo, o, kWave));
-            hi = fmax(hi, __shfl_xor(hi, o, kWave));
-        }
-        if (lane == leader) {
-            atomicAdd(&band_count[kl], (int)__popcll(grp));
-            atomic_min_pos_double(&band_th[2 * kl], lo);
-            atomic_max_pos_double(&band_th[2 * kl + 1], hi);
-        }
-        todo &= ~grp;
-    }
-}
-
-__global__ void k_scatter(int64_t n, const int *cell, const int *cell_start, int *cell_fill, int *order)
+// The points of every cell, in any order (counting the cell's count back down).
+__global__ void k_scatter(int64_t n, const int *cell, const int *cell_start, int *cell_count, int *order)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     int c = cell[i];
-    int pos = cell_start[c] + atomicAdd(&cell_fill[c], 1);
+    int pos = cell_start[c] + atomicSub(&cell_count[c], 1) - 1;
     order[pos] = (int)i;
 }
 
@@ -248,54 +372,46 @@ __global__ void k_sort_cells(int64_t ncells, const int *cell_start, int *order)
     }
 }
 
-__global__ void k_gather_points(int64_t n, const int *perm, const double *xyz, const double *w,
-                                double *x, double *y, double *z, double *ws)
+// The catalogue in index order, and the doubled-band arrays: index-order point i of band k (first
+// point s_k, n_k points) is stored at 2 s_k + (i - s_k) and again n_k positions later.
+__global__ void k_gather_points(int64_t n, const int *perm, const double *xyz, const double *w, const int *band,
+                                const Band *bands, double *x, double *y, double *z, double *ws, int *bs, int *permdbl,
+                                double *wdbl)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    int64_t j = perm[i];
+    const int j = perm[i], k = band[j];
     x[i] = xyz[j];
     y[i] = xyz[n + j];
     z[i] = xyz[2 * n + j];
-    ws[i] = w ? w[j] : 1.0;
+    const double wj = w ? w[j] : 1.0;
+    ws[i] = wj;
+    bs[i] = k;
+    const int64_t np = bands[k].npts, q = (int64_t)bands[k].pt_start + i;
+    permdbl[q] = j;
+    permdbl[q + np] = j;
+    if (w) {
+        wdbl[q] = wj;
+        wdbl[q + np] = wj;
+    }
 }
 
-__global__ void k_gather_values(int64_t n, int nmaps, const int *perm, const double *wsorted,
-                                const double *xv, double *v)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    int64_t j = perm[i];
-    double w = wsorted[i];
-    for (int m = 0; m < nmaps; ++m) v[(size_t)m * n + i] = w * xv[(size_t)m * n + j];
-}
-
-// Doubled-band layout: index-order point i of band k (first point s_k, n_k points) is
-// stored at 2 s_k + (i - s_k) and again n_k positions later.
-template <class T>
-__global__ void k_double_bands(int64_t n, const int *band, const Band *bands, const T *in, T *out)
+// Values w x in index order and the doubled-band records of every map.
+__global__ void k_values(int64_t n, int nmaps, const int *perm, const int *band, const Band *bands, const double *x,
+                         const double *y, const double *z, const double *w, const double *xv, double *v, double4 *rec)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
+    const int64_t j = perm[i];
     const Band &bd = bands[band[i]];
-    const int64_t q = 2 * (int64_t)bd.pt_start + (i - bd.pt_start);
-    const T v = in[i];
-    out[q] = v;
-    out[q + bd.npts] = v;
-}
-
-__global__ void k_records(int64_t n, int nmaps, const int *band, const Band *bands, const double *x,
-                          const double *y, const double *z, const double *v, double4 *rec)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const Band &bd = bands[band[i]];
-    const int64_t q = 2 * (int64_t)bd.pt_start + (i - bd.pt_start);
-    const double xi = x[i], yi = y[i], zi = z[i];
+    const int64_t np = bd.npts, q = (int64_t)bd.pt_start + i;
+    const double xi = x[i], yi = y[i], zi = z[i], wi = w[i];
     for (int m = 0; m < nmaps; ++m) {
-        const double4 r = make_double4(xi, yi, zi, v[(size_t)m * n + i]);
+        const double val = wi * xv[(size_t)m * n + j];
+        v[(size_t)m * n + i] = val;
+        const double4 r = make_double4(xi, yi, zi, val);
         rec[(size_t)m * 2 * n + q] = r;
-        rec[(size_t)m * 2 * n + q + bd.npts] = r;
+        rec[(size_t)m * 2 * n + q + np] = r;
     }
 }
 
@@ -339,24 +455,6 @@ __global__ void k_value_matrix(int64_t n, int nmaps, int ldv, const int *band, c
     }
 }
 
-__global__ void k_gather_int(int64_t n, const int *perm, const int *in, int *out)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] = in[perm[i]];
-}
-
-__global__ void k_fill_double(double *p, int64_t n, double v)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
-__global__ void k_fill_int(int *p, int64_t n, int v)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
 // ---- exclusive scan of int counts (n < 2^31 total) -----------------------------------
 
 constexpr int kScanThreads = 256;
@@ -397,39 +495,37 @@ __global__ void k_scan_add(int *out, int64_t n, const int *tile_offsets)
     if (i < n) out[i] += tile_offsets[i / kScanTile];
 }
 
-// out[i] = sum_{k<i} in[k] for i in [0, n) (the caller stores the total in out[n]).
-static z3_status exclusive_scan(const int *in, int64_t n, int *out, hipStream_t s)
+// Scratch ints of exclusive_scan over n counts.
+static int64_t scan_ints(int64_t n)
 {
-    int64_t tiles = (n + kScanTile - 1) / kScanTile;
-    if (tiles < 1) tiles = 1;
-    const size_t bytes = (size_t)(tiles + 1) * sizeof(int);
-    // both partial-sum buffers are released (stream-ordered) on every path out
-    struct Tmp {
-        int *p = nullptr;
-        hipStream_t s;
-        ~Tmp() { if (p) (void)hipFreeAsync(p, s); }
-    } sums{nullptr, s}, offs{nullptr, s};
-    z3_status st = alloc_allowed(bytes, "scan alloc");
-    if (st == Z3_OK) st = check_hip(hipMallocAsync((void **)&sums.p, bytes, s), "scan alloc");
-    if (st != Z3_OK) return st;
-    hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)tiles), dim3(kScanThreads), 0, s, in, n, out, sums.p);
-    if ((st = check_launch("k_scan_tiles")) != Z3_OK) return st;
-    if (tiles > 1) {
-        st = alloc_allowed(bytes, "scan alloc");
-        if (st == Z3_OK) st = check_hip(hipMallocAsync((void **)&offs.p, bytes, s), "scan alloc");
-        if (st != Z3_OK) return st;
-        if ((st = exclusive_scan(sums.p, tiles, offs.p, s)) != Z3_OK) return st;
-        hipLaunchKernelGGL(k_scan_add, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, out, n, offs.p);
-        if ((st = check_launch("k_scan_add")) != Z3_OK) return st;
+    int64_t total = 0;
+    for (int64_t tiles = (n + kScanTile - 1) / kScanTile;; tiles = (tiles + kScanTile - 1) / kScanTile) {
+        total += 2 * (tiles + 1);
+        if (tiles <= 1) return total;
     }
-    return Z3_OK;
 }
 
+// out[i] = sum_{k<i} in[k] for i in [0, n); tmp holds scan_ints(n).
+static z3_status exclusive_scan(const int *in, int64_t n, int *out, int *tmp, hipStream_t s)
+{
+    const int64_t tiles = n > kScanTile ? (n + kScanTile - 1) / kScanTile : 1;
+    int *sums = tmp, *offs = tmp + tiles + 1;
+    hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)tiles), dim3(kScanThreads), 0, s, in, n, out, sums);
+    z3_status st = check_launch("k_scan_tiles");
+    if (st != Z3_OK || tiles == 1) return st;
+    if ((st = exclusive_scan(sums, tiles, offs, offs + tiles + 1, s)) != Z3_OK) return st;
+    hipLaunchKernelGGL(k_scan_add, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, out, n, offs);
+    return check_launch("k_scan_add");
+}
+
+// The index's arrays go back to the idle blocks: no work that uses them may be in flight.
 static void free_ptrs(z3_index idx)
 {
-    void *ps[] = {idx->d_edges, idx->d_bands, idx->d_cell_start, idx->d_x, idx->d_y, idx->d_z,
-                  idx->d_w, idx->d_perm, idx->d_band, idx->d_wdbl, idx->d_permdbl, idx->d_v, idx->d_rec,
-                  idx->d_vgrp, idx->d_vmat64, idx->d_vmat32, idx->cap_ws, idx->d_phi_bounds, idx->d_phi_tab};
+    void *blocks[] = {idx->d_edges, idx->d_bands, idx->d_cell_start, idx->d_x, idx->d_y, idx->d_z, idx->d_w,
+                      idx->d_perm, idx->d_band, idx->d_wdbl, idx->d_permdbl, idx->d_v, idx->d_rec, idx->d_vgrp,
+                      idx->d_vmat64, idx->d_vmat32};
+    for (void *p : blocks) return_block(p);
+    void *ps[] = {idx->cap_ws, idx->d_phi_bounds, idx->d_phi_tab};
     for (void *p : ps)
         if (p) (void)hipFree(p);
     for (void *p : idx->cap_retired) (void)hipFree(p);
@@ -448,10 +544,7 @@ template <class T>
 static z3_status dalloc(T **p, size_t count, const char *what)
 {
     *p = nullptr;
-    const size_t bytes = (count ? count : 1) * sizeof(T);
-    const z3_status st = alloc_allowed(bytes, what);
-    if (st != Z3_OK) return st;
-    return check_hip(hipMalloc((void **)p, bytes), what);
+    return device_block((void **)p, (count ? count : 1) * sizeof(T), what);
 }
 
 static inline unsigned grid_for(int64_t n) { return (unsigned)((n + 255) / 256 > 0 ? (n + 255) / 256 : 1); }
@@ -472,32 +565,45 @@ z3_status build_index_impl(int64_t n, const double *xyz, const double *w, int nb
         delete idx;
         return code;
     };
-    // plane: the [2][n] positions become [3][n] with z = 0 (freed on return; every path
-    // out of this function synchronises the stream first)
-    struct TmpBuf {
-        double *p = nullptr;
-        ~TmpBuf() { if (p) (void)hipFree(p); }
-    } xyz3;
+    // temporaries: given back on return (every path out of this function synchronises the
+    // stream first)
+    struct Temps {
+        void *p[10] = {};
+        int count = 0;
+        void *pin = nullptr;
+        ~Temps()
+        {
+            for (int i = 0; i < count; ++i) return_block(p[i]);
+            pinned_give(pin);
+        }
+    } tmp;
+    auto temp = [&](auto **p, size_t count, const char *what) {
+        const z3_status e = dalloc(p, count, what);
+        if (e == Z3_OK) tmp.p[tmp.count++] = *p;
+        return e;
+    };
+    if ((st = pinned_take(&tmp.pin)) != Z3_OK) return bail(st);
+    // plane: the [2][n] positions become [3][n] with z = 0
     if (planar && n > 0) {
-        if ((st = dalloc(&xyz3.p, 3 * (size_t)n, "alloc plane positions")) != Z3_OK) return bail(st);
-        hipLaunchKernelGGL(k_plane_xyz, dim3(grid_for(n)), dim3(256), 0, s, xyz, n, xyz3.p);
+        double *xyz3 = nullptr;
+        if ((st = temp(&xyz3, 3 * (size_t)n, "alloc plane positions")) != Z3_OK) return bail(st);
+        hipLaunchKernelGGL(k_plane_xyz, dim3(grid_for(n)), dim3(256), 0, s, xyz, n, xyz3);
         if ((st = check_launch("k_plane_xyz")) != Z3_OK) return bail(st);
-        xyz = xyz3.p;
+        xyz = xyz3;
     }
     // plane: bounding box of the points (x0 = min x, y0 = min y, extents lx, ly)
     double lx = 0.0, ly = 0.0, scale = 0.0;
     if (planar && n > 0) {
-        const int nblk = (int)std::min<int64_t>((n + 255) / 256, 1024);
+        const int nblk = (int)std::min<int64_t>((n + 255) / 256, kPinnedBytes / (4 * sizeof(double)));
         double *d_part = nullptr;
-        if ((st = dalloc(&d_part, 4 * (size_t)nblk, "alloc plane range")) != Z3_OK) return bail(st);
+        if ((st = temp(&d_part, 4 * (size_t)nblk, "alloc plane range")) != Z3_OK) return bail(st);
         hipLaunchKernelGGL(k_plane_range, dim3(nblk), dim3(256), 0, s, xyz, n, d_part);
         st = check_launch("k_plane_range");
-        std::vector<double> part(4 * (size_t)nblk);
+        const double *part = static_cast<const double *>(tmp.pin);
         if (st == Z3_OK)
-            st = check_hip(hipMemcpyAsync(part.data(), d_part, part.size() * sizeof(double), hipMemcpyDeviceToHost, s),
+            st = check_hip(hipMemcpyAsync(tmp.pin, d_part, 4 * (size_t)nblk * sizeof(double), hipMemcpyDeviceToHost, s),
                            "copy plane range");
         if (st == Z3_OK) st = check_hip(hipStreamSynchronize(s), "sync");
-        (void)hipFree(d_part);
         if (st != Z3_OK) return bail(st);
         double v[4] = {INFINITY, -INFINITY, INFINITY, -INFINITY};
         for (int b = 0; b < nblk; ++b) {
@@ -536,18 +642,17 @@ z3_status build_index_impl(int64_t n, const double *xyz, const double *w, int nb
         double r = 2.0 * asin(std::min(1.0, sqrt(e) / 2.0));
         idx->edges.rad_out[b] = r * (1.0 + 1e-9) + 1e-12;
     }
+    double *d_range = nullptr;
     if ((st = dalloc(&idx->d_edges, 1, "alloc edges")) != Z3_OK) return bail(st);
-    if ((st = check_hip(hipMemcpyAsync(idx->d_edges, &idx->edges, sizeof(EdgeTab), hipMemcpyHostToDevice, s),
-                        "copy edges")) != Z3_OK)
-        return bail(st);
+    if ((st = temp(&d_range, 3, "alloc range")) != Z3_OK) return bail(st);
+    hipLaunchKernelGGL(k_index_begin, dim3(1), dim3(256), 0, s, idx->edges, idx->d_edges, d_range);
+    if ((st = check_launch("k_index_begin")) != Z3_OK) return bail(st);
 
     // ---- band height; sky positions: colatitude range and unit-length check --------------
     // Sky positions must be unit vectors: the windows are angular while membership is the
     // chord test on the raw vectors, and the windows' guards (1e-9 relative) cover a
     // deviation | |r|^2 - 1 | of up to kMaxNormDev only.
     double h = cell_size;
-    double *d_range = nullptr;
-    if ((st = dalloc(&d_range, 3, "alloc range")) != Z3_OK) return bail(st);
     double area = 1.0;
     if (planar) {
         // the same 1.4 x mean spacing as on the sphere
@@ -556,22 +661,20 @@ z3_status build_index_impl(int64_t n, const double *xyz, const double *w, int nb
         if (!(area > 0.0)) area = 1.0;
         if (h <= 0.0) h = Z3_BAND_HEIGHT_FACTOR * sqrt(area / (double)std::max<int64_t>(n, 1));
     } else {
-        double rg[3] = {kPi, 0.0, 0.0};
-        st = check_hip(hipMemcpyAsync(d_range, rg, sizeof(rg), hipMemcpyHostToDevice, s), "copy range");
-        if (st == Z3_OK && n > 0) {
+        const double *rg = static_cast<const double *>(tmp.pin);
+        if (n > 0) {
             unsigned g = grid_for(n) < 2048u ? grid_for(n) : 2048u;
             hipLaunchKernelGGL(k_sky_range, dim3(g), dim3(256), 0, s, xyz, n, d_range);
             st = check_launch("k_sky_range");
         }
-        if (st == Z3_OK) st = check_hip(hipMemcpyAsync(rg, d_range, sizeof(rg), hipMemcpyDeviceToHost, s), "copy range");
+        if (st == Z3_OK)
+            st = check_hip(hipMemcpyAsync(tmp.pin, d_range, 3 * sizeof(double), hipMemcpyDeviceToHost, s), "copy range");
         if (st == Z3_OK) st = check_hip(hipStreamSynchronize(s), "sync");
-        if (st != Z3_OK) { (void)hipFree(d_range); return bail(st); }
-        if (!(rg[2] <= kMaxNormDev)) {
-            (void)hipFree(d_range);
+        if (st != Z3_OK) return bail(st);
+        if (!(rg[2] <= kMaxNormDev))
             return bail(fail(Z3_ERR_INVALID_ARG,
                              "z3_build_index: positions are not unit vectors (max | |r|^2 - 1 | = %g, limit %g)", rg[2],
                              kMaxNormDev));
-        }
         area = 2.0 * kPi * (cos(std::min(rg[0], rg[1])) - cos(std::max(rg[0], rg[1])));
         if (!(area > 0.0)) area = 1e-12;
         if (h <= 0.0) {
@@ -584,7 +687,6 @@ z3_status build_index_impl(int64_t n, const double *xyz, const double *w, int nb
             h = Z3_BAND_HEIGHT_FACTOR * sqrt(area / (double)std::max<int64_t>(n, 1));
         }
     }
-    (void)hipFree(d_range);
     idx->density = (double)n / area;
     int nbands = 1;
     if (planar) {
@@ -601,125 +703,75 @@ z3_status build_index_impl(int64_t n, const double *xyz, const double *w, int nb
     idx->nbands = nbands;
 
     // ---- bands -------------------------------------------------------------------------
-    int *d_band = nullptr, *d_band_count = nullptr, *d_cell = nullptr, *d_cell_count = nullptr;
+    // At most 4 n + nbands cells (a band without points has one); the scan below also covers the
+    // entry after the last cell, which holds n.
+    const int64_t cells_max = (int64_t)kCellsPerPoint * n + nbands;
+    if (2 * n >= (int64_t)0x7fffffff) return bail(fail(Z3_ERR_OVERFLOW, "z3_build_index: too many points or cells"));
+    int *d_band = nullptr, *d_band_count = nullptr, *d_cell = nullptr, *d_cell_count = nullptr, *d_scan = nullptr;
+    int *d_stats = nullptr;
     double *d_phi = nullptr, *d_band_th = nullptr;
-    auto cleanup_tmp = [&]() {
-        void *ps[] = {d_band, d_band_count, d_cell, d_cell_count, d_phi, d_band_th};
-        for (void *p : ps)
-            if (p) (void)hipFree(p);
+    if ((st = temp(&d_band, n, "alloc band")) != Z3_OK) return bail(st);
+    if ((st = temp(&d_phi, n, "alloc phi")) != Z3_OK) return bail(st);
+    if ((st = temp(&d_band_count, (size_t)nbands + 2, "alloc band count")) != Z3_OK) return bail(st);
+    if ((st = temp(&d_band_th, 2 * (size_t)nbands, "alloc band theta")) != Z3_OK) return bail(st);
+    if ((st = temp(&d_cell, n, "alloc cell")) != Z3_OK) return bail(st);
+    if ((st = temp(&d_cell_count, cells_max + 1, "alloc cell count")) != Z3_OK) return bail(st);
+    if ((st = temp(&d_scan, scan_ints(cells_max + 1), "scan alloc")) != Z3_OK) return bail(st);
+    if ((st = dalloc(&idx->d_bands, nbands, "alloc bands")) != Z3_OK) return bail(st);
+    if ((st = dalloc(&idx->d_cell_start, cells_max + 1, "alloc cell start")) != Z3_OK) return bail(st);
+    d_stats = d_band_count + nbands;
+    hipLaunchKernelGGL(k_clear_counts, dim3(std::min(grid_for(std::max<int64_t>(cells_max + 1, nbands)), 8192u)), dim3(256),
+                       0, s, d_band_count, d_band_th, nbands, planar ? INFINITY : 4.0, d_cell_count, cells_max + 1);
+    const BandRule rule{1.0 / h, idx->plane_x0, idx->plane_y0, idx->plane_sx, planar ? INFINITY : 4.0, nbands};
+    st = planar ? launch_band_of_point<true>(xyz, n, rule, d_band, d_phi, d_band_count, d_band_th, s)
+                : launch_band_of_point<false>(xyz, n, rule, d_band, d_phi, d_band_count, d_band_th, s);
+    if (st != Z3_OK) return bail(st);
+    hipLaunchKernelGGL(k_band_table, dim3(1), dim3(kTableThreads), 0, s, nbands, h, d_band_count, d_band_th,
+                       idx->d_bands, d_stats);
+    if ((st = check_launch("k_band_table")) != Z3_OK) return bail(st);
+    const int *stats = static_cast<const int *>(tmp.pin);
+    auto read_stats = [&]() {
+        z3_status e = check_hip(hipMemcpyAsync(tmp.pin, d_stats, 2 * sizeof(int), hipMemcpyDeviceToHost, s), "copy");
+        return e == Z3_OK ? check_hip(hipStreamSynchronize(s), "sync") : e;
     };
-    auto bail2 = [&](z3_status code) {
-        (void)hipStreamSynchronize(s);
-        cleanup_tmp();
-        return bail(code);
-    };
-    if ((st = dalloc(&d_band, n, "alloc band")) != Z3_OK) return bail2(st);
-    if ((st = dalloc(&d_phi, n, "alloc phi")) != Z3_OK) return bail2(st);
-    if ((st = dalloc(&d_band_count, nbands, "alloc band count")) != Z3_OK) return bail2(st);
-    if ((st = dalloc(&d_band_th, 2 * (size_t)nbands, "alloc band theta")) != Z3_OK) return bail2(st);
-    hipLaunchKernelGGL(k_fill_int, dim3(grid_for(nbands)), dim3(256), 0, s, d_band_count, (int64_t)nbands, 0);
-    // th_lo starts at +big, th_hi at 0
-    hipLaunchKernelGGL(k_init_band_th, dim3((unsigned)((nbands + 255) / 256)), dim3(256), 0, s, d_band_th, nbands,
-                       planar ? INFINITY : 4.0);
-    if ((st = check_launch("k_init_band_th")) != Z3_OK) return bail2(st);
-    if (n > 0 && planar) {
-        hipLaunchKernelGGL(k_band_of_point_plane, dim3(grid_for(n)), dim3(256), 0, s, xyz, n, idx->plane_y0, 1.0 / h,
-                           idx->plane_x0, idx->plane_sx, nbands, d_band, d_phi, d_band_count, d_band_th);
-        if ((st = check_launch("k_band_of_point_plane")) != Z3_OK) return bail2(st);
-    } else if (n > 0) {
-        hipLaunchKernelGGL(k_band_of_point, dim3(grid_for(n)), dim3(256), 0, s, xyz, n, 1.0 / h, nbands, d_band,
-                           d_phi, d_band_count, d_band_th);
-        if ((st = check_launch("k_band_of_point")) != Z3_OK) return bail2(st);
+    if (cells_max >= (int64_t)0x7fffffff) {
+        // near the range's end: the exact number of cells decides (the table's count of them
+        // wraps below zero when it is beyond), before any kernel indexes them
+        if ((st = read_stats()) != Z3_OK) return bail(st);
+        if (stats[0] < 0 || stats[0] == 0x7fffffff)
+            return bail(fail(Z3_ERR_OVERFLOW, "z3_build_index: too many points or cells"));
     }
-    std::vector<int> bcount(nbands);
-    std::vector<double> bth(2 * (size_t)nbands);
-    st = check_hip(hipMemcpyAsync(bcount.data(), d_band_count, nbands * sizeof(int), hipMemcpyDeviceToHost, s), "copy");
-    if (st == Z3_OK)
-        st = check_hip(hipMemcpyAsync(bth.data(), d_band_th, bth.size() * sizeof(double), hipMemcpyDeviceToHost, s), "copy");
-    if (st == Z3_OK) st = check_hip(hipStreamSynchronize(s), "sync");
-    if (st != Z3_OK) return bail2(st);
-
-    // the multipole kernel addresses a band's doubled records (64 B per point) with 32-bit
-    // byte offsets
-    for (int k = 0; k < nbands; ++k)
-        if ((int64_t)bcount[k] * 64 > (int64_t)UINT32_MAX)
-            return bail2(fail(Z3_ERR_UNSUPPORTED, "z3_build_index: %d points in one latitude band", bcount[k]));
-    std::vector<Band> bands(nbands);
-    int64_t pt = 0, cells = 0;
-    for (int k = 0; k < nbands; ++k) {
-        Band &b = bands[k];
-        std::memset(&b, 0, sizeof(Band));
-        b.npts = bcount[k];
-        b.pt_start = (int)pt;
-        b.ncell = (int)std::max<int64_t>(1, (int64_t)kCellsPerPoint * b.npts);
-        b.cell_off = (int)cells;
-        b.cells_per_rad = (float)((double)b.ncell / kTwoPi);
-        double lo = b.npts ? bth[2 * k] : k * h, hi = b.npts ? bth[2 * k + 1] : k * h;
-        b.th_lo = lo;
-        b.th_hi = hi;
-        b.sh_lo = sin(0.5 * lo); b.ch_lo = cos(0.5 * lo);
-        b.sh_hi = sin(0.5 * hi); b.ch_hi = cos(0.5 * hi);
-        double slo = sin(lo), shi = sin(hi);
-        double smin = std::min(slo, shi);
-        double smax = (lo <= 0.5 * kPi && hi >= 0.5 * kPi) ? 1.0 : std::max(slo, shi);
-        b.inv_smin = smin > 0.0 ? (float)(1.0 / smin) : INFINITY;
-        b.inv_smax = smax > 0.0 ? (float)(1.0 / smax) : INFINITY;
-        pt += b.npts;
-        cells += b.ncell;
-    }
-    if (cells >= (int64_t)0x7fffffff || 2 * n >= (int64_t)0x7fffffff)
-        return bail2(fail(Z3_ERR_OVERFLOW, "z3_build_index: too many points or cells"));
-    idx->ncells = cells;
-    if ((st = dalloc(&idx->d_bands, nbands, "alloc bands")) != Z3_OK) return bail2(st);
-    st = check_hip(hipMemcpyAsync(idx->d_bands, bands.data(), nbands * sizeof(Band), hipMemcpyHostToDevice, s),
-                   "copy bands");
-    if (st != Z3_OK) return bail2(st);
 
     // ---- cells, sort -----------------------------------------------------------------------
-    if ((st = dalloc(&d_cell, n, "alloc cell")) != Z3_OK) return bail2(st);
-    if ((st = dalloc(&d_cell_count, cells + 1, "alloc cell count")) != Z3_OK) return bail2(st);
-    if ((st = dalloc(&idx->d_cell_start, cells + 1, "alloc cell start")) != Z3_OK) return bail2(st);
-    hipLaunchKernelGGL(k_fill_int, dim3(grid_for(cells + 1)), dim3(256), 0, s, d_cell_count, cells + 1, 0);
-    if (n > 0) {
+    if ((st = dalloc(&idx->d_perm, n, "alloc perm")) != Z3_OK) return bail(st);
+    if ((st = dalloc(&idx->d_x, n, "alloc x")) != Z3_OK) return bail(st);
+    if ((st = dalloc(&idx->d_y, n, "alloc y")) != Z3_OK) return bail(st);
+    if ((st = dalloc(&idx->d_z, n, "alloc z")) != Z3_OK) return bail(st);
+    if ((st = dalloc(&idx->d_w, n, "alloc w")) != Z3_OK) return bail(st);
+    idx->unit_w = (w == nullptr);
+    if ((st = dalloc(&idx->d_band, n, "alloc band")) != Z3_OK) return bail(st);
+    if ((st = dalloc(&idx->d_permdbl, 2 * n, "alloc perm2")) != Z3_OK) return bail(st);
+    if (!idx->unit_w && (st = dalloc(&idx->d_wdbl, 2 * n, "alloc w2")) != Z3_OK) return bail(st);
+    if (n > 0)
         hipLaunchKernelGGL(k_cell_of_point, dim3(grid_for(n)), dim3(256), 0, s, n, d_band, d_phi, idx->d_bands,
                            d_cell, d_cell_count);
-        if ((st = check_launch("k_cell_of_point")) != Z3_OK) return bail2(st);
-    }
-    if ((st = exclusive_scan(d_cell_count, cells, idx->d_cell_start, s)) != Z3_OK) return bail2(st);
-    // cell_start[cells] = n (bands are contiguous and cover all points)
-    hipLaunchKernelGGL(k_set_int, dim3(1), dim3(1), 0, s, idx->d_cell_start + cells, (int)n);
-    if ((st = check_launch("k_set_int")) != Z3_OK) return bail2(st);
-    if ((st = dalloc(&idx->d_perm, n, "alloc perm")) != Z3_OK) return bail2(st);
-    hipLaunchKernelGGL(k_fill_int, dim3(grid_for(cells + 1)), dim3(256), 0, s, d_cell_count, cells + 1, 0);
+    if ((st = exclusive_scan(d_cell_count, cells_max + 1, idx->d_cell_start, d_scan, s)) != Z3_OK) return bail(st);
     if (n > 0) {
         hipLaunchKernelGGL(k_scatter, dim3(grid_for(n)), dim3(256), 0, s, n, d_cell, idx->d_cell_start,
                            d_cell_count, idx->d_perm);
-        hipLaunchKernelGGL(k_sort_cells, dim3(grid_for(cells)), dim3(256), 0, s, cells, idx->d_cell_start,
+        hipLaunchKernelGGL(k_sort_cells, dim3(grid_for(cells_max)), dim3(256), 0, s, cells_max, idx->d_cell_start,
                            idx->d_perm);
-        if ((st = check_launch("k_scatter/k_sort_cells")) != Z3_OK) return bail2(st);
+        hipLaunchKernelGGL(k_gather_points, dim3(grid_for(n)), dim3(256), 0, s, n, idx->d_perm, xyz, w, d_band,
+                           idx->d_bands, idx->d_x, idx->d_y, idx->d_z, idx->d_w, idx->d_band, idx->d_permdbl,
+                           idx->d_wdbl);
     }
-    if ((st = dalloc(&idx->d_x, n, "alloc x")) != Z3_OK) return bail2(st);
-    if ((st = dalloc(&idx->d_y, n, "alloc y")) != Z3_OK) return bail2(st);
-    if ((st = dalloc(&idx->d_z, n, "alloc z")) != Z3_OK) return bail2(st);
-    if ((st = dalloc(&idx->d_w, n, "alloc w")) != Z3_OK) return bail2(st);
-    idx->unit_w = (w == nullptr);
-    if ((st = dalloc(&idx->d_band, n, "alloc band")) != Z3_OK) return bail2(st);
-    if ((st = dalloc(&idx->d_permdbl, 2 * n, "alloc perm2")) != Z3_OK) return bail2(st);
-    if (!idx->unit_w && (st = dalloc(&idx->d_wdbl, 2 * n, "alloc w2")) != Z3_OK) return bail2(st);
-    if (n > 0) {
-        hipLaunchKernelGGL(k_gather_points, dim3(grid_for(n)), dim3(256), 0, s, n, idx->d_perm, xyz, w, idx->d_x,
-                           idx->d_y, idx->d_z, idx->d_w);
-        hipLaunchKernelGGL(k_gather_int, dim3(grid_for(n)), dim3(256), 0, s, n, idx->d_perm, d_band, idx->d_band);
-        hipLaunchKernelGGL(k_double_bands<int>, dim3(grid_for(n)), dim3(256), 0, s, n, idx->d_band, idx->d_bands,
-                           idx->d_perm, idx->d_permdbl);
-        if (!idx->unit_w)
-            hipLaunchKernelGGL(k_double_bands<double>, dim3(grid_for(n)), dim3(256), 0, s, n, idx->d_band,
-                               idx->d_bands, idx->d_w, idx->d_wdbl);
-        if ((st = check_launch("k_gather_points")) != Z3_OK) return bail2(st);
-    }
-    st = check_hip(hipStreamSynchronize(s), "sync");
-    cleanup_tmp();
-    if (st != Z3_OK) return bail(st);
+    if ((st = check_launch("k_gather_points")) != Z3_OK) return bail(st);
+    if ((st = read_stats()) != Z3_OK) return bail(st);
+    idx->ncells = stats[0];
+    // the multipole kernel addresses a band's doubled records (64 B per point) with 32-bit
+    // byte offsets
+    if ((int64_t)stats[1] * 64 > (int64_t)UINT32_MAX)
+        return bail(fail(Z3_ERR_UNSUPPORTED, "z3_build_index: %d points in one latitude band", stats[1]));
     *out = idx;
     return Z3_OK;
 }
@@ -730,11 +782,9 @@ static z3_status fill_values(z3_index idx, int nmaps, const double *x, hipStream
 {
     z3_status st;
     if (idx->n == 0) return Z3_OK;
-    hipLaunchKernelGGL(k_gather_values, dim3(grid_for(idx->n)), dim3(256), 0, s, idx->n, nmaps, idx->d_perm,
-                       idx->d_w, x, idx->d_v);
-    hipLaunchKernelGGL(k_records, dim3(grid_for(idx->n)), dim3(256), 0, s, idx->n, nmaps, idx->d_band,
-                       idx->d_bands, idx->d_x, idx->d_y, idx->d_z, idx->d_v, idx->d_rec);
-    if ((st = check_launch("k_gather_values/k_records")) != Z3_OK) return st;
+    hipLaunchKernelGGL(k_values, dim3(grid_for(idx->n)), dim3(256), 0, s, idx->n, nmaps, idx->d_perm, idx->d_band,
+                       idx->d_bands, idx->d_x, idx->d_y, idx->d_z, idx->d_w, x, idx->d_v, idx->d_rec);
+    if ((st = check_launch("k_values")) != Z3_OK) return st;
     if (nmaps > 1) {
         hipLaunchKernelGGL(k_group_values, dim3(grid_for(idx->n)), dim3(256), 0, s, idx->n, nmaps, idx->d_band,
                            idx->d_bands, idx->d_v, idx->d_vgrp);
@@ -756,12 +806,17 @@ z3_status update_values_impl(z3_index idx, const double *x, hipStream_t s)
 z3_status set_values_impl(z3_index idx, int nmaps, const double *x, hipStream_t s)
 {
     z3_status st;
-    (void)hipStreamSynchronize(s);  // earlier work may still read the old values
-    if (idx->d_v) { (void)hipFree(idx->d_v); idx->d_v = nullptr; }
-    if (idx->d_rec) { (void)hipFree(idx->d_rec); idx->d_rec = nullptr; }
-    if (idx->d_vgrp) { (void)hipFree(idx->d_vgrp); idx->d_vgrp = nullptr; }
-    if (idx->d_vmat64) { (void)hipFree(idx->d_vmat64); idx->d_vmat64 = nullptr; }
-    if (idx->d_vmat32) { (void)hipFree(idx->d_vmat32); idx->d_vmat32 = nullptr; }
+    if (idx->d_v) {
+        // earlier work, on any stream, may still read the old values
+        (void)hipDeviceSynchronize();
+        void *old[] = {idx->d_v, idx->d_rec, idx->d_vgrp, idx->d_vmat64, idx->d_vmat32};
+        for (void *p : old) return_block(p);
+        idx->d_v = nullptr;
+        idx->d_rec = nullptr;
+        idx->d_vgrp = nullptr;
+        idx->d_vmat64 = nullptr;
+        idx->d_vmat32 = nullptr;
+    }
     idx->nmaps = 0;
     idx->ngroups = 0;
     for (auto &row : idx->batch_shape_tuned)

@@ -133,6 +133,15 @@ z3_status check_launch(const char *what);
 // Z3_ERR_OUT_OF_MEMORY if `bytes` exceed the device allocation limit (z3_set_device_alloc_limit)
 z3_status alloc_allowed(size_t bytes, const char *what);
 
+// device memory of the indexes, kept between them (z3_api.hip); a block may be returned only
+// when no work that uses it is in flight
+z3_status device_block(void **p, size_t bytes, const char *what);
+void return_block(void *p);
+// a pinned host buffer of kPinnedBytes
+constexpr size_t kPinnedBytes = 32768;
+z3_status pinned_take(void **p);
+void pinned_give(void *p);
+
 // index kernels (z3_index.hip)
 z3_status build_index_impl(int64_t n, const double *xyz, const double *w, int nbins,
                            const double *edges, double cell_size, hipStream_t s, z3_index *out,
