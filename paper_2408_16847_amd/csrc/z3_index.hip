@@ -582,7 +582,6 @@ z3_status build_index_impl(int64_t n, const double *xyz, const double *w, int nb
         if (e == Z3_OK) tmp.p[tmp.count++] = *p;
         return e;
     };
-    if ((st = pinned_take(&tmp.pin)) != Z3_OK) return bail(st);
     // plane: the [2][n] positions become [3][n] with z = 0
     if (planar && n > 0) {
         double *xyz3 = nullptr;
@@ -597,6 +596,7 @@ z3_status build_index_impl(int64_t n, const double *xyz, const double *w, int nb
         const int nblk = (int)std::min<int64_t>((n + 255) / 256, kPinnedBytes / (4 * sizeof(double)));
         double *d_part = nullptr;
         if ((st = temp(&d_part, 4 * (size_t)nblk, "alloc plane range")) != Z3_OK) return bail(st);
+        if ((st = pinned_take(&tmp.pin)) != Z3_OK) return bail(st);
         hipLaunchKernelGGL(k_plane_range, dim3(nblk), dim3(256), 0, s, xyz, n, d_part);
         st = check_launch("k_plane_range");
         const double *part = static_cast<const double *>(tmp.pin);
@@ -645,6 +645,7 @@ z3_status build_index_impl(int64_t n, const double *xyz, const double *w, int nb
     double *d_range = nullptr;
     if ((st = dalloc(&idx->d_edges, 1, "alloc edges")) != Z3_OK) return bail(st);
     if ((st = temp(&d_range, 3, "alloc range")) != Z3_OK) return bail(st);
+    if (!tmp.pin && (st = pinned_take(&tmp.pin)) != Z3_OK) return bail(st);
     hipLaunchKernelGGL(k_index_begin, dim3(1), dim3(256), 0, s, idx->edges, idx->d_edges, d_range);
     if ((st = check_launch("k_index_begin")) != Z3_OK) return bail(st);
 
