@@ -1382,7 +1382,7 @@ Z3_API z3_status z3_fftlog_a_functions(int N, const double *Pk, double k_min, do
     if (nmodels == 0) return Z3_OK;
     if (!Pk || !F || !theta || !out) return fail(Z3_ERR_INVALID_ARG, "z3_fftlog_a_functions: NULL pointer");
     const hipStream_t s = as_stream(stream);
-    int chunk = nmodels < 65535 ? nmodels : 65535;  // one grid z index per model of a pass
+    int chunk = nmodels < 21845 ? nmodels : 21845;  // one grid z index per factor pair and model of a pass
     if (workspace) {
         if (reinterpret_cast<uintptr_t>(workspace) % 256)
             return fail(Z3_ERR_INVALID_ARG, "z3_fftlog_a_functions: workspace not 256-byte aligned");

@@ -105,8 +105,8 @@ struct FftlogArgs {
     const double *theta;
     double2 *cg;              // [4][ld]: c_s g(a_s)
     double2 *a;               // [4][ld]: a_s
-    double2 *U;               // [4][T][ld]
-    double2 *Uw;              // [4][T][ldw]: omega_m U[.][N/2 + m], m = 0..N/2
+    double2 *U;               // [4][ld][T]
+    double2 *Uw;              // [4][ldw][T]: omega_m U[N/2 + m][.], m = 0..N/2
     double2 *E;               // [nchi][ldh]: e^{-i t deta ln chi_j}, t = 0..N
 };
 
@@ -158,74 +158,83 @@ __global__ __launch_bounds__(64) void k_fftlog_coeffs(FftlogArgs g)
     g.a[(size_t)f * g.ld + s] = a;
 }
 
-// U[f][i][s] = c_s g(a_s) theta_i^{-(1 + a_s + mt)} and its weighted upper half Uw; one thread
-// per (factor, angle, s < Ns)
-__global__ void k_fftlog_operands(FftlogArgs g)
+// Two tables in one launch:
+//   U[f][s][i] = c_s g(a_s) theta_i^{-(1 + a_s + mt)} and its weighted upper half Uw [f][m][i],
+//   one thread per (factor, s < Ns, angle);
+//   E[j][t] = e^{-i t deta ln chi_j}, t = 0..N, the threads after those.
+__global__ void k_fftlog_tables(FftlogArgs g)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)4 * g.T * g.Ns) return;
-    const int s = (int)(t % g.Ns), i = (int)((t / g.Ns) % g.T), f = (int)(t / ((int64_t)g.Ns * g.T));
-    const int mt = g.f[f].mt;
-    const double2 cg = g.cg[(size_t)f * g.ld + s], a = g.a[(size_t)f * g.ld + s];
-    const double lt = log(g.theta[i]);
-    const double2 u = cmul(cg, cexp(make_double2(-(1.0 + a.x + mt) * lt, -a.y * lt)));
-    g.U[((size_t)f * g.T + i) * g.ld + s] = u;
-    const int m = s - g.N / 2;
-    if (m >= 0) {
-        const double om = m ? 2.0 : 1.0;
-        g.Uw[((size_t)f * g.T + i) * g.ldw + m] = make_double2(om * u.x, om * u.y);
+    const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, nu = (int64_t)4 * g.T * g.Ns;
+    if (t0 < nu) {
+        const int i = (int)(t0 % g.T), s = (int)((t0 / g.T) % g.Ns), f = (int)(t0 / ((int64_t)g.Ns * g.T));
+        const int mt = g.f[f].mt;
+        const double2 cg = g.cg[(size_t)f * g.ld + s], a = g.a[(size_t)f * g.ld + s];
+        const double lt = log(g.theta[i]);
+        const double2 u = cmul(cg, cexp(make_double2(-(1.0 + a.x + mt) * lt, -a.y * lt)));
+        g.U[((size_t)f * g.ld + s) * g.T + i] = u;
+        const int m = s - g.N / 2;
+        if (m >= 0) {
+            const double om = m ? 2.0 : 1.0;
+            g.Uw[((size_t)f * g.ldw + m) * g.T + i] = make_double2(om * u.x, om * u.y);
+        }
+    } else if (t0 - nu < (int64_t)g.nchi * (g.N + 1)) {
+        const int64_t e = t0 - nu;
+        const int t = (int)(e % (g.N + 1)), j = (int)(e / (g.N + 1));
+        const double lc = log(g.chi_min) + j * g.dlnchi;
+        double sn, cs;
+        sincos(-(double)t * fftlog_deta(g.N, g.k_min, g.k_max) * lc, &sn, &cs);
+        g.E[(size_t)j * g.ldh + t] = make_double2(cs, sn);
     }
 }
 
-// E[j][t] = e^{-i t deta ln chi_j}, t = 0..N
-__global__ void k_fftlog_phases(FftlogArgs g)
-{
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (int64_t)g.nchi * (g.N + 1)) return;
-    const int t = (int)(e % (g.N + 1)), j = (int)(e / (g.N + 1));
-    const double lc = log(g.chi_min) + j * g.dlnchi;
-    double sn, cs;
-    sincos(-(double)t * fftlog_deta(g.N, g.k_min, g.k_max) * lc, &sn, &cs);
-    g.E[(size_t)j * g.ldh + t] = make_double2(cs, sn);
-}
-
-// weights of each (factor pair q, model b): D[q][b][j] = w_j F_b(chi_j) chi_j^{-1} chi_j^{-(2 + nu1 + nu2)}
+// weights of each (factor pair q, model b): D[j][q][b] = w_j F_b(chi_j) chi_j^{-1} chi_j^{-(2 + nu1 + nu2)}
 // (w_j the trapezoid weights in ln chi)
 __global__ void k_fftlog_weights(const double *F, int nchi, int nmodels, double chi_min, double dlnchi,
                                  double3 nusum, double *D)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= (int64_t)nchi * nmodels * 3) return;
-    const int j = (int)(t % nchi);
-    const int q = (int)(t / ((int64_t)nchi * nmodels));
-    const int64_t bj = t % ((int64_t)nchi * nmodels);
+    const int b = (int)(t % nmodels), q = (int)(t / nmodels % 3), j = (int)(t / ((int64_t)nmodels * 3));
     const double lc = log(chi_min) + j * dlnchi;
     const double w = (j == 0 || j == nchi - 1) ? 0.5 * dlnchi : dlnchi;
     const double e = q == 0 ? nusum.x : q == 1 ? nusum.y : nusum.z;
-    D[t] = w * F[bj] * exp(-(3.0 + e) * lc);
+    D[t] = w * F[(size_t)b * nchi + j] * exp(-(3.0 + e) * lc);
 }
 
-// Batched FP64 matrix product C[b] = A[b] B[b], elements addressed by strides (a Hankel operand
-// H_{kj} = h[k + j] is b_k = b_j = 1).  A is complex; by TAG:
+// Batched FP64 matrix product C[q][b] = A[q][b] B[q][b] over the factor pairs q and the models b of
+// a pass (blockIdx.z = q models + b), elements addressed by strides (a Hankel operand
+// H_{ik} = h[i + k] is a_i = a_k = 1).  One launch takes all three factor pairs: one pair of 128
+// models (640 blocks of four waves at N = 256, T = 64) left the chip a third empty and ended in
+// a tail of its own.  A is complex; by TAG:
 //   1: B real, C complex, and each row i of C also written, conjugated, at row -i (the mirror
 //      h(-t) = conj h(t))
 //   2: B and C complex
 //   3: B complex, only Re C computed and stored (as double)
 // Each wave computes a (16 RM) x 16 tile of C (RM 16 x 16 MFMA tiles sharing one B fragment).
-// With KSPLIT the block's four waves share one tile and split the k range (k-steps of 8, wave w
-// takes steps w, w + 4, ...; partial sums added through LDS in a fixed order, so results are
+// With KSPLIT the block's four waves share one tile and split the k range (runs of 8, wave w
+// takes runs w, w + 4, ...; partial sums added through LDS in a fixed order, so results are
 // deterministic): for products with few output tiles and a long k range.  Without it the four
-// waves take four neighbouring column tiles.  The fragments of the next k-step are loaded
+// waves take neighbouring tiles of their own.  The fragments of the next k-steps are loaded
 // before the current step's MFMAs.  Operand lane
-// layout of v_mfma_f64_16x16x4f64: A row / B column = lane & 15, k = lane >> 4.
+// layout of v_mfma_f64_16x16x4f64: A row / B column = lane & 15, k = lane >> 4.  Every operand is
+// laid out with its rows (A) or columns (B) contiguous: a 16-byte load then returns 64 bytes
+// per cycle, where rows far apart return one lane's 16 (counters at 1024 models, rows apart: 55
+// cycles per load, the data return 94% busy, the matrix cores 72%).  Waves of 32 x 16 tiles:
+// 64 x 16 leave the last row tile of N + 1 = 257 a block of its own (128 models 255 us in all,
+// 32 x 16 237 us).  Whole calls at N = 256, 512 chi, 64 angles, this and the form before: 4
+// models 192 -> 98 us, 128 343 -> 237 us, 1024 1827 -> 1428 us.
 struct CGemm {
     const double2 *A;
     int64_t a_i, a_k, a_b;
     const void *B;
     int64_t b_k, b_j, b_b;
-    void *C;
-    int64_t c_i, c_j, c_b;
+    int64_t c_i, c_j;
     int M, N, K;
+    int nb;                    // models
+    int64_t a_q[3], b_q[3];    // operands of factor pair q
+    void *c_q[3];              // results of factor pair q, models c_bq apart
+    int64_t c_bq[3];
+    int wc_shift;
 };
 
 template <int TAG, int RM, bool KSPLIT>
@@ -234,37 +243,44 @@ __global__ __launch_bounds__(256) void k_cgemm(CGemm g)
     constexpr bool BREAL = TAG == 1, CREAL = TAG == 3;
     typedef typename std::conditional<BREAL, double, double2>::type BT;
     __shared__ double red[3][8][64];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int j0 = KSPLIT ? blockIdx.x * 16 : (blockIdx.x * 4 + w) * 16;
-    if (!KSPLIT && j0 >= g.N) return;  // no barrier in this mode
-    const int i0 = blockIdx.y * 16 * RM, b = blockIdx.z;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // without KSPLIT the block's waves are 2^wc_shift columns by 4 >> wc_shift rows of tiles
+    const int wr = w >> g.wc_shift, wc = w & ((1 << g.wc_shift) - 1);
+    const int j0 = (KSPLIT ? blockIdx.x : (blockIdx.x << g.wc_shift) + wc) * 16;
+    const int i0 = (KSPLIT ? blockIdx.y : blockIdx.y * (4 >> g.wc_shift) + wr) * 16 * RM;
+    if (!KSPLIT && (j0 >= g.N || i0 >= g.M)) return;  // no barrier in this mode
+    const int fq = (int)blockIdx.z / g.nb, b = (int)blockIdx.z - fq * g.nb;
     const int r = lane & 15, q = lane >> 4;
     const int nrm = min(RM, (g.M - i0 + 15) / 16);  // block-uniform count of live row tiles
-    const double2 *A = g.A + (size_t)b * g.a_b;
-    const BT *B = static_cast<const BT *>(g.B) + (size_t)b * g.b_b;
+    const double2 *A = g.A + (size_t)b * g.a_b + g.a_q[fq];
+    const BT *B = static_cast<const BT *>(g.B) + (size_t)b * g.b_b + g.b_q[fq];
     const int jb = j0 + r;
     const bool jin = jb < g.N;
 
     // per-lane row pointers of A and column pointer of B; k offsets stay 32-bit (k a_k, k b_k
-    // < 2^31 for every product launched)
+    // < 2^31 for every product launched).  Rows and columns past the matrix read its first ones
+    // and are not stored, so only the last k-step, past K, is masked: a zero B with the A of K - 1
     const double2 *Ar[RM];
-    bool rok[RM];
 #pragma unroll
     for (int u = 0; u < RM; ++u) {
         const int i = i0 + 16 * u + r;
-        rok[u] = u < nrm && i < g.M;
-        Ar[u] = A + (rok[u] ? (size_t)i * g.a_i : 0);
+        Ar[u] = A + (u < nrm && i < g.M ? (size_t)i * g.a_i : 0);
     }
     const BT *Bc = B + (jin ? (size_t)jb * g.b_j : 0);
     const int ak = (int)g.a_k, bk = (int)g.b_k;
-    auto load = [&](int k, double2 (&av)[RM], BT &bv) {
-        const bool kin = k < g.K;
+    auto load = [&](int kb, double2 (&av)[RM], BT &bv) __attribute__((always_inline)) {
+        if (kb + 4 <= g.K) {  // wave-uniform
+            const int k = kb + q;
 #pragma unroll
-        for (int u = 0; u < RM; ++u) av[u] = (kin && rok[u]) ? Ar[u][k * ak] : make_double2(0.0, 0.0);
-        if constexpr (BREAL)
-            bv = (kin && jin) ? Bc[k * bk] : 0.0;
-        else
-            bv = (kin && jin) ? Bc[k * bk] : make_double2(0.0, 0.0);
+            for (int u = 0; u < RM; ++u) av[u] = Ar[u][k * ak];
+            bv = Bc[k * bk];
+        } else if (kb < g.K) {
+            const int k = min(kb + q, g.K - 1);
+#pragma unroll
+            for (int u = 0; u < RM; ++u) av[u] = Ar[u][k * ak];
+            bv = Bc[k * bk];
+            if (kb + q >= g.K) bv = BT{};
+        }
     };
     v4d re[RM], im[RM];
 #pragma unroll
@@ -281,13 +297,15 @@ __global__ __launch_bounds__(256) void k_cgemm(CGemm g)
             for (int u = 0; u < RM; ++u)
                 if (u < nrm) im[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u].y, bv, im[u], 0, 0, 0);
         } else if constexpr (CREAL) {
+            const double nby = -bv.y;
 #pragma unroll
             for (int u = 0; u < RM; ++u)
                 if (u < nrm) re[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u].x, bv.x, re[u], 0, 0, 0);
 #pragma unroll
             for (int u = 0; u < RM; ++u)
-                if (u < nrm) re[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(-av[u].y, bv.y, re[u], 0, 0, 0);
+                if (u < nrm) re[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u].y, nby, re[u], 0, 0, 0);
         } else {
+            const double nby = -bv.y;
 #pragma unroll
             for (int u = 0; u < RM; ++u)
                 if (u < nrm) {
@@ -297,22 +315,26 @@ __global__ __launch_bounds__(256) void k_cgemm(CGemm g)
 #pragma unroll
             for (int u = 0; u < RM; ++u)
                 if (u < nrm) {
-                    re[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(-av[u].y, bv.y, re[u], 0, 0, 0);
+                    re[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u].y, nby, re[u], 0, 0, 0);
                     im[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u].y, bv.x, im[u], 0, 0, 0);
                 }
         }
     };
-    double2 a0[RM], a1[RM];
-    BT b0, b1;
-    constexpr int kstride = KSPLIT ? 32 : 8;
-    int k0 = KSPLIT ? 8 * w : 0;
-    load(k0 + q, a0, b0);
-    for (; k0 < g.K; k0 += kstride) {
-        load(k0 + 4 + q, a1, b1);
-        step(a0, b0);
-        if (k0 + 4 >= g.K) break;
-        load(k0 + kstride + q, a0, b0);
-        step(a1, b1);
+    // k-steps requested ahead: the single-tile product has two MFMAs a step, which hide little
+    // (one step ahead it took 19 us at N = 256, 512 chi and 128 models)
+    constexpr int PD = RM == 1 ? 8 : 2;
+    double2 af[PD][RM];
+    BT bf[PD];
+    // step n of this wave starts at k = kat(n)
+    auto kat = [&](int n) { return KSPLIT ? 32 * (n >> 1) + 8 * w + 4 * (n & 1) : 4 * n; };
+#pragma unroll
+    for (int d = 0; d < PD - 1; ++d) load(kat(d), af[d], bf[d]);
+    for (int n = 0; kat(n) < g.K; n += PD) {
+#pragma unroll
+        for (int d = 0; d < PD; ++d) {
+            load(kat(n + d + PD - 1), af[(d + PD - 1) % PD], bf[(d + PD - 1) % PD]);
+            if (kat(n + d) < g.K) step(af[d], bf[d]);
+        }
     }
     // partial sums of waves 1..3 added into wave 0's, one row tile at a time
     for (int u = 0; KSPLIT && u < RM; ++u) {
@@ -343,11 +365,11 @@ __global__ __launch_bounds__(256) void k_cgemm(CGemm g)
         for (int k = 0; k < 4; ++k) {
             const int i = i0 + 16 * u + 4 * k + q;
             if (i >= g.M) continue;
-            const int64_t o = (size_t)b * g.c_b + i * g.c_i + jb * g.c_j;
+            const int64_t o = (size_t)b * g.c_bq[fq] + i * g.c_i + jb * g.c_j;
             if constexpr (CREAL) {
-                static_cast<double *>(g.C)[o] = re[u][k];
+                static_cast<double *>(g.c_q[fq])[o] = re[u][k];
             } else {
-                double2 *C = static_cast<double2 *>(g.C);
+                double2 *C = static_cast<double2 *>(g.c_q[fq]);
                 C[o] = make_double2(re[u][k], im[u][k]);
                 if constexpr (TAG == 1) C[o - 2 * i * g.c_i] = make_double2(re[u][k], -im[u][k]);
             }
@@ -356,11 +378,13 @@ __global__ __launch_bounds__(256) void k_cgemm(CGemm g)
 }
 
 template <int TAG, int RM, bool KSPLIT>
-static z3_status cgemm(const CGemm &g, int batch, hipStream_t s)
+static z3_status cgemm(const CGemm &g0, int pairs, hipStream_t s)
 {
-    const int cols = KSPLIT ? 16 : 64;
-    const dim3 grid((unsigned)((g.N + cols - 1) / cols), (unsigned)((g.M + 16 * RM - 1) / (16 * RM)),
-                    (unsigned)batch);
+    // waves side by side along the columns, as far as there are column tiles
+    CGemm g = g0;
+    g.wc_shift = g.N > 32 ? 2 : (g.N > 16 ? 1 : 0);
+    const int cols = KSPLIT ? 16 : 16 << g.wc_shift, rows = 16 * RM * (KSPLIT ? 1 : 4 >> g.wc_shift);
+    const dim3 grid((unsigned)((g.N + cols - 1) / cols), (unsigned)((g.M + rows - 1) / rows), (unsigned)(pairs * g.nb));
     hipEvent_t ev0 = nullptr;
     if (TAG == 2) profile_begin(s, &ev0);
     hipLaunchKernelGGL((k_cgemm<TAG, RM, KSPLIT>), grid, dim3(256), 0, s, g);
@@ -368,18 +392,16 @@ static z3_status cgemm(const CGemm &g, int batch, hipStream_t s)
     return check_launch("k_cgemm");
 }
 
-// out[b][0] = I0, out[b][1] = I1 + I1^T, out[b][2] = I2 (I real, [b][3][T][T])
-__global__ void k_fftlog_out(const double *I, int T, int nmodels, double *out)
+// out[b][1] = I1 + I1^T (out [b][3][T][T], I1 [b][T][T]; the other two are written directly)
+__global__ void k_fftlog_out(const double *I1, int T, int nmodels, double *out)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t per = (int64_t)T * T;
-    if (t >= per * 3 * nmodels) return;
-    const int64_t b = t / (3 * per), rem = t % (3 * per);
-    const int p = (int)(rem / per), ij = (int)(rem % per), i = ij / T, j = ij % T;
-    const double *Ib = I + (size_t)(b * 3 + p) * per;
-    double v = Ib[ij];
-    if (p == 1) v += Ib[(size_t)j * T + i];
-    out[t] = v;
+    if (t >= per * nmodels) return;
+    const int64_t b = t / per;
+    const int ij = (int)(t % per), i = ij / T, j = ij % T;
+    const double *Ib = I1 + (size_t)b * per;
+    out[(size_t)(3 * b + 1) * per + ij] = Ib[ij] + Ib[(size_t)j * T + i];
 }
 
 struct FftlogLayout {
@@ -437,12 +459,9 @@ z3_status fftlog_impl(int N, const double *Pk, double k_min, double k_max, const
     hipLaunchKernelGGL(k_fftlog_coeffs, dim3((unsigned)g.Ns, 4), dim3(64), 0, s, g);
     z3_status st = check_launch("k_fftlog_coeffs");
     if (st != Z3_OK) return st;
-    const int64_t nop = (int64_t)4 * T * g.Ns;
-    hipLaunchKernelGGL(k_fftlog_operands, dim3((unsigned)((nop + 255) / 256)), dim3(256), 0, s, g);
-    if ((st = check_launch("k_fftlog_operands")) != Z3_OK) return st;
-    const int64_t nph = (int64_t)nchi * (N + 1);
-    hipLaunchKernelGGL(k_fftlog_phases, dim3((unsigned)((nph + 255) / 256)), dim3(256), 0, s, g);
-    if ((st = check_launch("k_fftlog_phases")) != Z3_OK) return st;
+    const int64_t ntab = (int64_t)4 * T * g.Ns + (int64_t)nchi * (N + 1);
+    hipLaunchKernelGGL(k_fftlog_tables, dim3((unsigned)((ntab + 255) / 256)), dim3(256), 0, s, g);
+    if ((st = check_launch("k_fftlog_tables")) != Z3_OK) return st;
     // factor pairs of A_0, A_1, A_2: (0,0)x(0,0), (1,1)x(1,-1), (2,0)x(2,0)
     const int f1[3] = {0, 1, 3}, f2[3] = {0, 2, 3};
     const double3 nusum = make_double3(nu[0] + nu[0], nu[1] + nu[2], nu[3] + nu[3]);
@@ -454,24 +473,22 @@ z3_status fftlog_impl(int N, const double *Pk, double k_min, double k_max, const
                            F + (size_t)b0 * nchi, nchi, nb, chi_min, g.dlnchi, nusum, D);
         if ((st = check_launch("k_fftlog_weights")) != Z3_OK) break;
         // h[col][N + t] = sum_j E[j][t] D[col][j] for t = 0..N, mirrored to N - t; col = (q, b)
-        CGemm mh{g.E, 1, ldh, 0, D, 1, (int64_t)nchi, 0, H + N, 1, ldt, 0, N + 1, 3 * nb, nchi};
+        CGemm mh{g.E, 1, ldh, 0, D, 3 * nb, 1, 0, 1, ldt, N + 1, 3 * nb, nchi, 1, {0, 0, 0}, {0, 0, 0},
+                 {H + N, nullptr, nullptr}, {0, 0, 0}};
         if ((st = cgemm<1, 1, true>(mh, 1, s)) != Z3_OK) break;
-        for (int q = 0; q < 3 && st == Z3_OK; ++q) {
-            // UA[b][q][i][s2] = sum_{m >= 0} Uw_f1[i][m] h[q][b][N/2 + m + s2]
-            CGemm m2{g.Uw + (size_t)f1[q] * T * ldw, ldw, 1, 0,
-                     H + (size_t)q * nb * ldt + N / 2, 1, 1, ldt,
-                     UA + (size_t)q * T * ld, ld, 1, 3 * T * ld, T, g.Ns, N / 2 + 1};
-            st = cgemm<2, 4, false>(m2, nb, s);
-            // Ire[b][q] = Re(UA[b][q] U_f2^T)
-            CGemm m3{UA + (size_t)q * T * ld, ld, 1, 3 * T * ld,
-                     g.U + (size_t)f2[q] * T * ld, 1, ld, 0,
-                     Ire + (size_t)q * T * T, (int64_t)T, 1, (int64_t)3 * T * T, T, T, g.Ns};
-            if (st == Z3_OK) st = cgemm<3, 4, true>(m3, nb, s);
-        }
-        if (st != Z3_OK) break;
-        const int64_t no = (int64_t)nb * 3 * T * T;
-        hipLaunchKernelGGL(k_fftlog_out, dim3((unsigned)((no + 255) / 256)), dim3(256), 0, s, Ire, T, nb,
-                           out + (size_t)b0 * 3 * T * T);
+        const int64_t TT = (int64_t)T * T, TL = (int64_t)T * ld, TW = (int64_t)T * ldw;
+        double *ob = out + (size_t)b0 * 3 * TT;
+        // UA[b][q][s2][i] = sum_{m >= 0} h[q][b][N/2 + m + s2] Uw_f1[m][i]
+        CGemm m2{H + N / 2, 1, 1, ldt, g.Uw, T, 1, 0, T, 1, g.Ns, T, N / 2 + 1, nb,
+                 {0, nb * ldt, 2 * nb * ldt}, {f1[0] * TW, f1[1] * TW, f1[2] * TW}, {UA, UA + TL, UA + 2 * TL},
+                 {3 * TL, 3 * TL, 3 * TL}};
+        if ((st = cgemm<2, 2, false>(m2, 3, s)) != Z3_OK) break;
+        // I[b][q][i][j] = Re sum_s UA[b][q][s][i] U_f2[s][j]: A_0 and A_2 as they are, A_1 still to
+        // be symmetrised
+        CGemm m3{UA, 1, T, 3 * TL, g.U, T, 1, 0, (int64_t)T, 1, T, T, g.Ns, nb, {0, TL, 2 * TL},
+                 {f2[0] * TL, f2[1] * TL, f2[2] * TL}, {ob, Ire, ob + 2 * TT}, {3 * TT, TT, 3 * TT}};
+        if ((st = cgemm<3, 2, false>(m3, 3, s)) != Z3_OK) break;
+        hipLaunchKernelGGL(k_fftlog_out, dim3((unsigned)((nb * TT + 255) / 256)), dim3(256), 0, s, Ire, T, nb, ob);
         st = check_launch("k_fftlog_out");
     }
     return st;
