@@ -16,48 +16,16 @@
 // harmonic row to LDS; after a block barrier every wave runs the MFMA steps for its own
 // maps over the whole group, 4 candidates per step: A = map values (16 maps x 4
 // candidates, read from the per-record value matrix), B = harmonic rows (4 candidates x
-// 16 columns, from LDS).  The shape (WPB, TI) is a tuning choice.
+// 16 columns, from LDS).  The shape (WPB, TI) is a tuning choice.  Bins of few pairs go many at
+// a time instead (z3_batch_bins.hip).
 //
 // Precision: FP64 path: FP64 harmonics, values and v_mfma_f64_16x16x4f64 accumulation.
 // Mixed path: harmonics computed in FP64 and rounded to FP32, FP32 values, and
 // v_mfma_f32_16x16x4f32; the FP32 sums over each run of 128 candidates are added into
 // FP64 bin sums.  Distances and bin decisions are FP64 on both paths (bit-exact pair sets).
-#include "z3_batch_device.h"
+#include "z3_batch.h"
 
 namespace z3 {
-
-typedef double v4d __attribute__((ext_vector_type(4)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-struct BatchArgs {
-    const double4 *rec;           // [2n] doubled records (x, y, z, .)
-    const void *vmat;             // [2n][ldv] doubled per-map values w * x (FP64 or FP32)
-    int ldv;                      // maps padded to a multiple of 32 (zeros)
-    const double *wdbl;           // [2n] doubled weights, or null for unit weights
-    const int *cell_start;
-    const Band *bands;
-    int nbands;
-    double inv_h;
-    const EdgeTab *edges;
-    int nb;
-    const double *px, *py, *pz;   // pivots (index order)
-    int64_t p0, p1;
-    int nmaps;                    // maps written (rows >= nmaps are padding)
-    int ntiles;                   // map tiles of one pivot (blocks per pivot)
-    void *stage;                  // [P][nb][nmaps][2 (m+1)] pivot-major multipoles (re, im per m)
-    double *W;                    // [nb][ldA] W_{p,b}, or null
-    int64_t ldA;
-    uint64_t *pair_total;
-    int nblocks;
-};
-
-// Block shapes the library is built with: waves per block, 16-map tiles per wave.
-struct BatchShape { int wpb, ti; };
-constexpr BatchShape kBatchShapes[] = {{4, 1}, {2, 2}, {2, 1}, {4, 2}};
-constexpr int kNumBatchShapes = sizeof(kBatchShapes) / sizeof(kBatchShapes[0]);
-
-template <bool F32> struct BatchT { typedef double T; typedef v4d V4; };
-template <> struct BatchT<true> { typedef float T; typedef v4f V4; };
 
 // Register budget: 3 waves per SIMD on the mixed path (measured faster than the
 // compiler's own choice), 2 on the FP64 path.
@@ -166,30 +134,7 @@ void k_multipoles_batch(BatchArgs a)
                 if (!unit_w) s_wc[tid] = in ? a.wdbl[j] : 0.0;
                 if (in) {
                     cnt += 1;
-                    const double u1 = fma(dx, f.nx, fma(dy, f.ny, dz * f.nz));
-                    const double u2 = fma(dx, f.ex, dy * f.ey);
-                    double c1, sn1;
-                    unit_bearing(u1, u2, c1, sn1);
-                    // cos(m phi) = T_m(cos phi), sin(m phi) = sin phi U_{m-1}(cos phi): the
-                    // three-term recurrence in FP64 on both paths (as cheap as FP32 on this
-                    // hardware, and free of the recurrence's error growth in FP32); the mixed
-                    // path rounds each harmonic to FP32 once
-                    h[0] = T(1);
-                    if constexpr (M >= 1) {
-                        const double tc = c1 + c1;
-                        double t2 = 1.0, t1 = c1, u2s = 0.0, u1s = sn1;
-                        h[1] = (T)t1;
-                        h[M + 1] = (T)u1s;
-#pragma unroll
-                        for (int m = 2; m <= M; ++m) {
-                            const double tm = fma(tc, t1, -t2);
-                            const double sm = fma(tc, u1s, -u2s);
-                            h[m] = (T)tm;
-                            h[M + m] = (T)sm;
-                            t2 = t1; t1 = tm;
-                            u2s = u1s; u1s = sm;
-                        }
-                    }
+                    harmonic_row<M>(f, dx, dy, dz, h);
                 }
 #pragma unroll
                 for (int c = 0; c < NC; ++c) s_h[hslot<HS>(tid, c)] = h[c];
@@ -421,18 +366,24 @@ z3_status launch_multipoles_batch(const z3_index_s *idx, int m_max, int prec, in
     a.ldA = ldA;
     a.pair_total = pair_total;
     a.nblocks = (int)nblk;
+    a.vmat_bytes = 0;
+    const bool many_bins = batch_many_bins(idx, f32);
+    if (many_bins) a.vmat_bytes = (uint32_t)(2 * (size_t)idx->n * a.ldv * (f32 ? 4 : 8));
     hipEvent_t ev0;
     profile_begin(s, &ev0);
     z3_status st = Z3_OK;
-    switch (m_max) {
+    if (many_bins)
+        st = launch_batch_bins(m_max, f32, shape, a, s);
+    else
+        switch (m_max) {
 #define Z3_CASE(MM) \
-    case MM: st = f32 ? launch_batch_m<MM, true>(shape, a, s) : launch_batch_m<MM, false>(shape, a, s); break;
-        Z3_CASE(0) Z3_CASE(1) Z3_CASE(2) Z3_CASE(3) Z3_CASE(4) Z3_CASE(5) Z3_CASE(6) Z3_CASE(7)
-        Z3_CASE(8) Z3_CASE(9) Z3_CASE(10) Z3_CASE(11) Z3_CASE(12) Z3_CASE(13) Z3_CASE(14)
-        Z3_CASE(15) Z3_CASE(16)
+        case MM: st = f32 ? launch_batch_m<MM, true>(shape, a, s) : launch_batch_m<MM, false>(shape, a, s); break;
+            Z3_CASE(0) Z3_CASE(1) Z3_CASE(2) Z3_CASE(3) Z3_CASE(4) Z3_CASE(5) Z3_CASE(6) Z3_CASE(7)
+            Z3_CASE(8) Z3_CASE(9) Z3_CASE(10) Z3_CASE(11) Z3_CASE(12) Z3_CASE(13) Z3_CASE(14)
+            Z3_CASE(15) Z3_CASE(16)
 #undef Z3_CASE
-    default: st = fail(Z3_ERR_UNSUPPORTED, "m_max=%d not compiled", m_max);
-    }
+        default: st = fail(Z3_ERR_UNSUPPORTED, "m_max=%d not compiled", m_max);
+        }
     if (st == Z3_OK) st = check_launch("k_multipoles_batch");
     profile_end(s, ev0);
     if (st != Z3_OK || !A) return st;

@@ -48,12 +48,16 @@ __device__ __forceinline__ double longitude(double x, double y)
 // ---- kernels ---------------------------------------------------------------------------
 
 // Colatitude range of the positions and their largest deviation | |r|^2 - 1 | from unit
-// length (non-finite -> +inf), one pass over the coordinates: a grid-stride extremum per
-// thread, a block reduction, one atomic per block and quantity.
-__global__ __launch_bounds__(256) void k_sky_range(const double *xyz, int64_t n, double *range /* [3] */)
+// length (non-finite -> +inf), and which 64ths of the longitude circle hold points (a bit each),
+// one pass over the coordinates: a grid-stride extremum per thread, a block reduction, one
+// atomic per block and quantity.
+__global__ __launch_bounds__(256) void k_sky_range(const double *xyz, int64_t n, double *range /* [3], sectors */)
 {
     __shared__ double smin[256], smax[256], sdev[256];
+    __shared__ unsigned long long ssec;
     double lo = 4.0, hi = 0.0, dev = 0.0;
+    unsigned long long sec = 0;
+    if (threadIdx.x == 0) ssec = 0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const double x = xyz[i], y = xyz[n + i], z = xyz[2 * n + i];
         const double th = colatitude(x, y, z);
@@ -62,11 +66,13 @@ __global__ __launch_bounds__(256) void k_sky_range(const double *xyz, int64_t n,
         double d = fabs((x * x + y * y + z * z) - 1.0);
         if (!(d <= 1e300)) d = INFINITY;
         dev = fmax(dev, d);
+        sec |= 1ull << (min(max((int)(longitude(x, y) * (64.0 / kTwoPi)), 0), 63));
     }
     smin[threadIdx.x] = lo;
     smax[threadIdx.x] = hi;
     sdev[threadIdx.x] = dev;
     __syncthreads();
+    atomicOr(&ssec, sec);
     for (int o = 128; o > 0; o >>= 1) {
         if ((int)threadIdx.x < o) {
             smin[threadIdx.x] = fmin(smin[threadIdx.x], smin[threadIdx.x + o]);
@@ -79,6 +85,7 @@ __global__ __launch_bounds__(256) void k_sky_range(const double *xyz, int64_t n,
         atomic_min_pos_double(&range[0], smin[0]);
         atomic_max_pos_double(&range[1], smax[0]);
         if (sdev[0] > 0.0) atomic_max_pos_double(&range[2], sdev[0]);
+        atomicOr(reinterpret_cast<unsigned long long *>(range + 3), ssec);
     }
 }
 
@@ -89,7 +96,7 @@ __global__ void k_index_begin(EdgeTab e, EdgeTab *edges, double *range)
     const double *src = reinterpret_cast<const double *>(&e);
     double *dst = reinterpret_cast<double *>(edges);
     for (int i = threadIdx.x; i < (int)(sizeof(EdgeTab) / sizeof(double)); i += blockDim.x) dst[i] = src[i];
-    if (threadIdx.x == 0) { range[0] = kPi; range[1] = 0.0; range[2] = 0.0; }
+    if (threadIdx.x == 0) { range[0] = kPi; range[1] = 0.0; range[2] = 0.0; range[3] = 0.0; }
 }
 
 // No points in any band or cell; the bands' colatitude ranges start empty, [lo0, 0].
@@ -644,7 +651,7 @@ z3_status build_index_impl(int64_t n, const double *xyz, const double *w, int nb
     }
     double *d_range = nullptr;
     if ((st = dalloc(&idx->d_edges, 1, "alloc edges")) != Z3_OK) return bail(st);
-    if ((st = temp(&d_range, 3, "alloc range")) != Z3_OK) return bail(st);
+    if ((st = temp(&d_range, 4, "alloc range")) != Z3_OK) return bail(st);
     if (!tmp.pin && (st = pinned_take(&tmp.pin)) != Z3_OK) return bail(st);
     hipLaunchKernelGGL(k_index_begin, dim3(1), dim3(256), 0, s, idx->edges, idx->d_edges, d_range);
     if ((st = check_launch("k_index_begin")) != Z3_OK) return bail(st);
@@ -669,7 +676,7 @@ z3_status build_index_impl(int64_t n, const double *xyz, const double *w, int nb
             st = check_launch("k_sky_range");
         }
         if (st == Z3_OK)
-            st = check_hip(hipMemcpyAsync(tmp.pin, d_range, 3 * sizeof(double), hipMemcpyDeviceToHost, s), "copy range");
+            st = check_hip(hipMemcpyAsync(tmp.pin, d_range, 4 * sizeof(double), hipMemcpyDeviceToHost, s), "copy range");
         if (st == Z3_OK) st = check_hip(hipStreamSynchronize(s), "sync");
         if (st != Z3_OK) return bail(st);
         if (!(rg[2] <= kMaxNormDev))
@@ -678,6 +685,9 @@ z3_status build_index_impl(int64_t n, const double *xyz, const double *w, int nb
                              kMaxNormDev));
         area = 2.0 * kPi * (cos(std::min(rg[0], rg[1])) - cos(std::max(rg[0], rg[1])));
         if (!(area > 0.0)) area = 1e-12;
+        uint64_t sectors;
+        __builtin_memcpy(&sectors, rg + 3, sizeof(sectors));
+        if (sectors) idx->sky_part = __builtin_popcountll(sectors) / 64.0;
         if (h <= 0.0) {
             // 1.4 x the mean point spacing: about two HEALPix rings per band (ring spacing
             // 2 / (3 Nside) rad at low latitudes, mean spacing ~1.023 / Nside).  Each band

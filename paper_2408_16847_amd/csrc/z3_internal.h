@@ -58,6 +58,7 @@ struct z3_index_s {
     int nbins = 0;
     double band_h = 0.0;
     double density = 0.0;             // points per unit area of the colatitude range (plane: of the bounding box)
+    double sky_part = 1.0;            // share of 64 longitude sectors that hold points (plane: 1)
     int nbands = 0;
     int64_t ncells = 0;
     z3::EdgeTab edges{};
