@@ -17,7 +17,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "z3_internal.h"
+#include "z3_device.h"
 
 namespace z3 {
 
@@ -478,9 +478,16 @@ static z3_status launch_pair(const PairArgs &c, bool f32, bool sym, int64_t nseg
 // ---- LDS-staged contraction of the pivot-major staging ------------------------------------
 // One block of kGramWaves waves per (pivot segment, map).  Tiles of kGramKP pivots of the
 // many-map kernel's pivot-major staging (one contiguous run of R = 2 (m_max + 1) rows per
-// pivot and bin) are staged in LDS as [pivot][bin][row], runs on consecutive lanes.  Every
-// wave then runs its (m, tile pair) units over the tile out of LDS, so each multipole is
-// fetched once per block and the staging needs no transpose.
+// pivot and bin) are staged in LDS, (re, im) pairs on consecutive lanes.  Every wave then runs
+// its (m, tile pair) units over the tile out of LDS, so each multipole is fetched once per
+// block and the staging needs no transpose.
+//
+// What bounds it: 64 maps of 197,000 pivots (15 bins, m_max 10) are 16.6 GB in FP32, 3.5 ms, and
+// 3.3 ms of MFMA, and the vector unit's split of v_p U_i costs about as much.  The tile's loads are
+// requested one tile ahead, so that they pass beside the products; an operand of 4 k-steps is one
+// 16-byte LDS read without bank conflicts instead of four scalar ones; and on the mixed path 2
+// blocks fit a CU (126 VGPRs).  With loads, barrier and products in turn it took 11.3 ms, now 6.5;
+// FP64 16.4 -> 9.5 ms.
 constexpr int kGramWaves = 8;
 constexpr int kGramThreads = kGramWaves * 64;
 constexpr int kGramKP = 16;                      // pivots per LDS tile (4 MFMA k-steps)
@@ -492,7 +499,9 @@ static size_t gram_tile_bytes(int nb, int R, bool f32)
 }
 
 // units per wave: the smallest compiled bound covering M1 x (tile pairs) units, else 0 (more
-// accumulators than a wave can hold at two waves per SIMD without spilling)
+// accumulators than a wave can hold at two waves per SIMD without spilling).  A tile then has
+// at most 7 or 9 (re, im) pairs per thread: 16 nb M1 <= 256 units / (T + 1), with T = 1 and at
+// most 17 units (m_max 16), T = 2 and at most 51, T >= 3.
 static int gram_upw(int nunits)
 {
     for (int u : {5, 9})
@@ -522,19 +531,42 @@ struct GramArgs {
     size_t v_stride;
     int nb, R, T, ntp, M1, nmaps, nunits;
     int seg;             // pivots per segment
-    int lpr_shift;       // PM staging: log2 of the lanes per (pivot, bin) run of R rows
     size_t tile_bytes;
     double *part;        // [seg][map][m][tile pair][256]
 };
 
+// The tile in LDS: entry e = 2 m nb + u of U_m at 16 pivots, so that the rows of an operand are
+// neighbours.  A lane's four pivots kq, 4 + kq, .. (one of each k-step) stand together, 16 bytes
+// in FP32, 32 in FP64, and the 16-byte slots of an entry are permuted by e so that a read by 16
+// rows touches every bank once.  gram_slot is the byte offset of pivot kq (in FP64: its slot of
+// k-steps 0 and 1; that of 2 and 3 is the offset ^ 16).
+template <bool F32>
+__device__ __forceinline__ int gram_slot(int e, int kq)
+{
+    return F32 ? 64 * e + 16 * (kq ^ (e >> 2 & 3)) : 128 * e + 16 * ((2 * kq) ^ (e >> 1 & 7));
+}
+
+__device__ __forceinline__ void gram_entries(const unsigned char *smem, int at, float (&u)[4])
+{
+    const float4 q = *reinterpret_cast<const float4 *>(smem + at);
+    u[0] = q.x; u[1] = q.y; u[2] = q.z; u[3] = q.w;
+}
+
+__device__ __forceinline__ void gram_entries(const unsigned char *smem, int at, double (&u)[4])
+{
+    const double2 q = *reinterpret_cast<const double2 *>(smem + at), r = *reinterpret_cast<const double2 *>(smem + (at ^ 16));
+    u[0] = q.x; u[1] = q.y; u[2] = r.x; u[3] = r.y;
+}
+
 template <bool F32, int UPW>
-__global__ __launch_bounds__(kGramThreads) void k_gram_lds(GramArgs g)
+__global__ __launch_bounds__(kGramThreads) __attribute__((amdgpu_waves_per_eu(F32 && UPW == 5 ? 4 : 2))) void k_gram_lds(GramArgs g)
 {
     typedef typename std::conditional<F32, float, double>::type T;
+    typedef typename std::conditional<F32, float2, double2>::type T2;
+    constexpr int NLD = UPW == 5 ? 7 : 9;  // (re, im) pairs of a tile per thread, see gram_upw
     extern __shared__ __align__(16) unsigned char smem[];
-    T *tile = reinterpret_cast<T *>(smem);                          // [kGramKP][nb][R]
     double *vt = reinterpret_cast<double *>(smem + g.tile_bytes);   // [kGramKP]
-    const int nb = g.nb, R = g.R, rowlen = nb * R;
+    const int nb = g.nb, R = g.R;
     // blocks are dealt round-robin to the 8 XCDs: each XCD gets a contiguous run of
     // (segment, map) units, so blocks reading neighbouring maps' runs share its L2
     const int64_t nblk = gridDim.x, bi = blockIdx.x, per = nblk / 8;
@@ -546,14 +578,15 @@ __global__ __launch_bounds__(kGramThreads) void k_gram_lds(GramArgs g)
     const T *src = static_cast<const T *>(g.src.base) + (size_t)map * g.src.map_stride;
     const double *v = g.v + (size_t)map * g.v_stride;
 
-    // this wave's units (m, tile pair) and, for each, the offsets within one pivot's LDS row
-    // of the A-operand and B-operand entries this lane supplies (-1: a padding row)
+    // this wave's units (m, tile pair) and, for each, where in LDS this lane's entries of the A
+    // and B operands stand (rows that pad a tile read entry 0: their results are never read)
     int um[UPW], offa[UPW], offb[UPW];
     v4d acc[UPW];
 #pragma unroll
     for (int j = 0; j < UPW; ++j) {
         const int uu = wave + kGramWaves * j;
-        um[j] = offa[j] = offb[j] = -1;
+        um[j] = -1;
+        offa[j] = offb[j] = gram_slot<F32>(0, kq);
         acc[j] = v4d{0.0, 0.0, 0.0, 0.0};
         if (uu < g.nunits) {
             const int m = uu / g.ntp;
@@ -562,79 +595,78 @@ __global__ __launch_bounds__(kGramThreads) void k_gram_lds(GramArgs g)
             const int J = I + r;
             const int ua = I * 16 + row, ub = J * 16 + row;
             um[j] = m;
-            if (ua < 2 * nb) { const int c = ua >= nb; offa[j] = (ua - c * nb) * R + 2 * m + c; }
-            if (ub < 2 * nb) { const int c = ub >= nb; offb[j] = (ub - c * nb) * R + 2 * m + c; }
+            if (ua < 2 * nb) offa[j] = gram_slot<F32>(2 * m * nb + ua, kq);
+            if (ub < 2 * nb) offb[j] = gram_slot<F32>(2 * m * nb + ub, kq);
         }
     }
 
+    // (re, im) pairs tid, tid + kGramThreads, .. of a tile
+    const int npr = nb * (R / 2);  // pairs of a pivot
+    uint32_t off[NLD], at[NLD];  // in memory, from its first pivot's row; in LDS: re, im << 16
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+        const int e = min(tid + i * kGramThreads, kGramKP * npr - 1), k = e / npr, b = (e - k * npr) / (R / 2);
+        const int m = e - k * npr - b * (R / 2), ks = k >> 2;
+        off[i] = tid + i * kGramThreads < kGramKP * npr ? (uint32_t)((k * g.src.sp + b * g.src.sb + 2 * m) * sizeof(T)) : 0xfffffff0u;
+        const int re = gram_slot<F32>(2 * m * nb + b, k & 3), im = gram_slot<F32>((2 * m + 1) * nb + b, k & 3);
+        const int part = F32 ? 4 * ks : 8 * (ks & 1), half = F32 ? 0 : 16 * (ks >> 1);
+        at[i] = (uint32_t)((re ^ half) + part) | (uint32_t)((im ^ half) + part) << 16;
+    }
+    T2 val[NLD];
+    double vval = 0.0;
+    // reads past the tile's last pivot give zeros: their offsets are past the view's end
+    auto load_tile = [&](int64_t p0, int np) __attribute__((always_inline)) {
+        const __amdgpu_buffer_rsrc_t rows = buffer_view(src + p0 * g.src.sp, (uint32_t)(np * g.src.sp * sizeof(T)));
+#pragma unroll
+        for (int i = 0; i < NLD; ++i) {
+            if constexpr (F32) val[i] = __builtin_bit_cast(T2, __builtin_amdgcn_raw_buffer_load_b64(rows, off[i], 0, 0));
+            else val[i] = __builtin_bit_cast(T2, __builtin_amdgcn_raw_buffer_load_b128(rows, off[i], 0, 0));
+        }
+        if (tid < kGramKP) vval = tid < np ? v[p0 + tid] : 0.0;
+    };
+
     const int64_t pbeg = seg * g.seg;
     const int64_t pend = min(g.npiv, pbeg + g.seg);
+    load_tile(pbeg, (int)min((int64_t)kGramKP, pend - pbeg));
     for (int64_t p0 = pbeg; p0 < pend; p0 += kGramKP) {
-        const int np = (int)min((int64_t)kGramKP, pend - p0);
         __syncthreads();  // the previous tile is consumed
-        // Each thread walks its elements (inner index b by `step`, wrapping into the outer
-        // index) with incremental addresses, and issues the global loads of 8 elements
-        // before it writes any of them to LDS, so their latencies overlap.
-        // runs of R rows per (pivot, bin), contiguous in memory: lanes along the run
-        const int step = kGramThreads >> g.lpr_shift;
-        const int r = tid & ((1 << g.lpr_shift) - 1);
-        const int kb0 = tid >> g.lpr_shift;
-        int k = kb0 / nb, b = kb0 - k * nb;
-        const T *ptr = src + (size_t)(p0 + k) * g.src.sp + (size_t)b * g.src.sb + r;
-        int li = kb0 * R + r;
-        const int64_t d_in = (int64_t)step * g.src.sb, d_wrap = g.src.sp - (int64_t)nb * g.src.sb;
-        while (k < kGramKP) {
-            T val[8];
-            int at[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                at[i] = -1;
-                if (k < kGramKP) {
-                    if (r < R) at[i] = li;
-                    val[i] = (k < np && r < R) ? *ptr : T(0);
-                    b += step;
-                    ptr += d_in;
-                    li += step * R;
-                    while (b >= nb) { b -= nb; ++k; ptr += d_wrap; }
-                }
+        for (int i = 0; i < NLD; ++i)
+            if (tid + i * kGramThreads < kGramKP * npr) {
+                *reinterpret_cast<T *>(smem + (at[i] & 0xffff)) = val[i].x;
+                *reinterpret_cast<T *>(smem + (at[i] >> 16)) = val[i].y;
             }
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (at[i] >= 0) tile[at[i]] = val[i];
-        }
-        if (tid < kGramKP) vt[tid] = tid < np ? v[p0 + tid] : 0.0;
+        if (tid < kGramKP) vt[tid] = vval;
         __syncthreads();
+        // the next tile is on its way while this one is multiplied
+        if (p0 + kGramKP < pend) load_tile(p0 + kGramKP, (int)min((int64_t)kGramKP, pend - p0 - kGramKP));
         double vk[4];
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) vk[ks] = vt[4 * ks + kq];
 #pragma unroll
         for (int j = 0; j < UPW; ++j) {
             if (um[j] < 0) continue;  // wave-uniform
+            T ua[4], ub[4];
+            gram_entries(smem, offa[j], ua);
+            gram_entries(smem, offb[j], ub);
             if constexpr (F32) {
                 // FP32 products and sums over the tile's pivots, then into the FP64 sum; the
                 // scaled operand v_p U_i is formed in FP64 and carried as FP32 hi + lo
                 v4f part = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
                 for (int ks = 0; ks < 4; ++ks) {
-                    const int base = (4 * ks + kq) * rowlen;
-                    const float ua = offa[j] >= 0 ? tile[base + offa[j]] : 0.0f;
-                    const float ub = offb[j] >= 0 ? tile[base + offb[j]] : 0.0f;
-                    const double av = (double)ua * vk[ks];
+                    const double av = (double)ua[ks] * vk[ks];
                     const float ahi = (float)av;
                     const float alo = (float)(av - (double)ahi);
-                    part = __builtin_amdgcn_mfma_f32_16x16x4f32(ahi, ub, part, 0, 0, 0);
-                    part = __builtin_amdgcn_mfma_f32_16x16x4f32(alo, ub, part, 0, 0, 0);
+                    part = __builtin_amdgcn_mfma_f32_16x16x4f32(ahi, ub[ks], part, 0, 0, 0);
+                    part = __builtin_amdgcn_mfma_f32_16x16x4f32(alo, ub[ks], part, 0, 0, 0);
                 }
 #pragma unroll
                 for (int k = 0; k < 4; ++k) acc[j][k] += (double)part[k];
             } else {
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {
-                    const int base = (4 * ks + kq) * rowlen;
-                    const double ua = offa[j] >= 0 ? tile[base + offa[j]] : 0.0;
-                    const double ub = offb[j] >= 0 ? tile[base + offb[j]] : 0.0;
-                    acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ua * vk[ks], ub, acc[j], 0, 0, 0);
-                }
+                for (int ks = 0; ks < 4; ++ks)
+                    acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ua[ks] * vk[ks], ub[ks], acc[j], 0, 0, 0);
             }
         }
     }
@@ -690,7 +722,6 @@ static z3_status contract_src(int64_t npiv, int m_max, int nbins, int prec, int 
         g.nmaps = nmaps;
         g.nunits = (m_max + 1) * ntp;
         g.seg = seg;
-        g.lpr_shift = g.R <= 32 ? 5 : 6;
         g.tile_bytes = gram_tile_bytes(nbins, g.R, f32);
         g.part = static_cast<double *>(partials);
         const int upw = gram_upw(g.nunits);
