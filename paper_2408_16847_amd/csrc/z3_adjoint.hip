@@ -41,8 +41,10 @@ struct PrepArgs {
 //     D(a) = sum_b H(a, b) conj(X(b)),
 // and the pivot term is Re sum_a X(a) E(a) = Re sum_a X(a) D(a) / 2, since
 // sum_a X(a) F(a) = conj(sum_a X(a) E(a)) (swap a and b).  NBT bounds nb (registers).
+// It reads A and writes D once; four waves per SIMD up to 16 bins keep more of those in flight than the
+// three that 129 registers left: 786,000 pivots x 15 bins, m_max 10 (4.2 GB) 1280 -> 1061 us.
 template <int NBT>
-__global__ __launch_bounds__(256) void k_adjoint_prep(PrepArgs a)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NBT <= 16 ? 4 : 2))) void k_adjoint_prep(PrepArgs a)
 {
     __shared__ double2 sH[NBT * NBT];
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -205,17 +207,33 @@ constexpr int adjoint_waves_per_eu()
     return K == 1 ? (M <= 10 ? 4 : (M <= 13 ? 3 : 2)) : (K == 2 && M <= 10 ? 3 : 2);
 }
 
+// Whether the next candidate's record is requested while the current one is worked on: where its
+// 8 registers do not spill at that occupancy.
+template <int M, int K>
+constexpr bool adjoint_record_ahead()
+{
+    return K == 1 || (K == 2 ? M != 10 : M <= 9);
+}
+
 // Per-wave LDS slice that gathers a window's contributions before they go to HBM: the
 // lanes of a wave walk overlapping ranges of the same band, so one window's pairs touch
 // only ~(window + 64) distinct neighbours.  kAggSlots doubles per wave, split among the K
 // maps.
 constexpr int kAggSlots = 1024;
 
-template <int M, int K, bool PLANAR = false>
+//
+// What bounds it: the FP64 work of a pair (about 60 operations) in lanes that wait for the
+// longest window of their wave, and the latency of the records.  JOIN walks a window's two segments
+// as one, so that lanes even out over their sum: 786,000 pixels x 15 bins (m_max 10, windows of 4 pairs)
+// 3.70 -> 3.35 ms; with windows of 9 and more pairs the bookkeeping costs more than that (3 maps, 6
+// bins to 400', 21.6 -> 24.0 ms).  Several bands at a time took the gain back.  With four or two maps
+// a lane the two forms are equal, and only the plain one is built.
+template <int M, int K, bool PLANAR, bool JOIN>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(adjoint_waves_per_eu<M, K>())))
 void k_adjoint_scatter(ScatterArgs a)
 {
     constexpr int SLOTS = kAggSlots / K;
+    constexpr bool AHEAD = adjoint_record_ahead<M, K>();
     __shared__ double agg_all[kBlock / kWave][K][SLOTS];
     double(*agg)[SLOTS] = agg_all[threadIdx.x / kWave];
     const int lane = threadIdx.x & (kWave - 1);
@@ -278,18 +296,36 @@ void k_adjoint_scatter(ScatterArgs a)
             else
                 band_window(bd, a.cell_start, f.th, f.sh, f.ch, f.inv_sp, f.phf, hav_out, hav_in, s0, l0, s1, l1);
             const int base = 2 * bd.pt_start;
+            // the window's two segments one after the other, or (JOIN) end to end
 #pragma unroll
-            for (int seg = 0; seg < 2; ++seg) {
+            for (int seg = 0; seg < (JOIN ? 1 : 2); ++seg) {
                 int j = base + (seg == 0 ? s0 : s1);
-                const int jend = j + (seg == 0 ? l0 : l1);
-                // the wave's span of this segment; inactive lanes do not widen it
-                const bool any = j < jend;
-                const int jlo = __builtin_amdgcn_readfirstlane(wave_min(any ? j : 0x7fffffff));
-                const int jhi = __builtin_amdgcn_readfirstlane(wave_max(any ? jend : -1));
-                if (jhi <= jlo) continue;
-                const bool use_lds = jhi - jlo <= SLOTS;
-                for (; j < jend; ++j) {
-                    const double4 r = rec[j];
+                int jend = j + (seg == 0 ? l0 : l1);
+                // the wave's span of each segment [jlo, jlo + len); inactive lanes do not widen it
+                int jlo[JOIN ? 2 : 1], len[JOIN ? 2 : 1], total = 0;
+#pragma unroll
+                for (int q = 0; q < (JOIN ? 2 : 1); ++q) {
+                    const int jq = q == 0 ? j : base + s1, jqend = q == 0 ? jend : base + s1 + l1;
+                    jlo[q] = __builtin_amdgcn_readfirstlane(wave_min(jq < jqend ? jq : 0x7fffffff));
+                    len[q] = max(__builtin_amdgcn_readfirstlane(wave_max(jq < jqend ? jqend : -1)) - jlo[q], 0);
+                    total += len[q];
+                }
+                if (total == 0) continue;
+                const bool use_lds = total <= SLOTS;
+                int slot0 = -jlo[0];  // record j adds to slot slot0 + j
+                bool second = false;
+                double4 next = double4{0.0, 0.0, 0.0, 0.0};
+                if constexpr (JOIN)
+                    if (j >= jend) { second = true; j = base + s1; jend = j + l1; slot0 = len[0] - jlo[1]; }
+                if (AHEAD && j < jend) next = rec[j];
+                while (j < jend) {
+                    const double4 r = AHEAD ? next : rec[j];
+                    const int jc = j, slot = slot0 + j;
+                    ++j;
+                    if constexpr (JOIN)
+                        if (j >= jend && !second) { second = true; j = base + s1; jend = j + l1; slot0 = len[0] - jlo[1]; }
+                    // (the last candidate again at the end: an empty second segment has no records)
+                    if constexpr (AHEAD) next = rec[j < jend ? j : jc];
                     const double dx = r.x - f.xp, dy = r.y - f.yp, dz = r.z - f.zp;
                     const double d2 = (dx * dx + dy * dy) + dz * dz;
                     if (d2 >= elo && d2 < ehi) {
@@ -315,15 +351,15 @@ void k_adjoint_scatter(ScatterArgs a)
                             }
                         }
                         if (!unit_w) {
-                            const double wj = a.wdbl[j];
+                            const double wj = a.wdbl[jc];
 #pragma unroll
                             for (int k = 0; k < K; ++k) acc[k] *= wj;
                         }
                         if (use_lds) {
 #pragma unroll
-                            for (int k = 0; k < K; ++k) atomicAdd(&agg[k][j - jlo], acc[k]);
+                            for (int k = 0; k < K; ++k) atomicAdd(&agg[k][slot], acc[k]);
                         } else {
-                            int t = j - base;
+                            int t = jc - base;
                             if (t >= bd.npts) t -= bd.npts;
 #pragma unroll
                             for (int k = 0; k < K; ++k)
@@ -335,18 +371,21 @@ void k_adjoint_scatter(ScatterArgs a)
                     // one global atomic per touched neighbour and map, and the slice is cleared
                     __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's LDS adds are done
                     __builtin_amdgcn_wave_barrier();
-                    for (int e = lane; e < jhi - jlo; e += kWave) {
-                        int t = jlo + e - base;
-                        if (t >= bd.npts) t -= bd.npts;
 #pragma unroll
-                        for (int k = 0; k < K; ++k) {
-                            const double val = agg[k][e];
-                            if (val != 0.0) {
-                                atomicAdd(&a.grad[(mp0 + k) * a.n_stride + bd.pt_start + t], val);
-                                agg[k][e] = 0.0;
+                    for (int q = 0; q < (JOIN ? 2 : 1); ++q)
+                        for (int e = lane; e < len[q]; e += kWave) {
+                            const int slot = q * len[0] + e;
+                            int t = jlo[q] + e - base;
+                            if (t >= bd.npts) t -= bd.npts;
+#pragma unroll
+                            for (int k = 0; k < K; ++k) {
+                                const double val = agg[k][slot];
+                                if (val != 0.0) {
+                                    atomicAdd(&a.grad[(mp0 + k) * a.n_stride + bd.pt_start + t], val);
+                                    agg[k][slot] = 0.0;
+                                }
                             }
                         }
-                    }
                     __builtin_amdgcn_s_waitcnt(0xc07f);
                     __builtin_amdgcn_wave_barrier();
                 }
@@ -361,32 +400,43 @@ __global__ void k_grad_to_catalogue(int64_t n, const int *perm, const double *gs
     if (i < n) grad[perm[i]] += gs[i];
 }
 
-// Maps in pairs (geometry shared by two maps per lane), an odd last map alone.
-template <int M>
-static void launch_scatter_m(const ScatterArgs &a, int nm, bool planar, hipStream_t s)
+// Maps in fours (geometry shared by the maps of a lane), then two, then an odd last one; from
+// m_max 12 in twos, since the coefficients of four spill.  Measured, whole gradients, fours / twos
+// (197,000 pixels, 12 bins): 8 maps m_max 11 9.7 / 11.0 ms, 4 maps m_max 12 5.37 / 5.38, 13
+// 6.9 / 5.1, 16 12.5 / 6.0 ms.  One map a lane joins a window's segments where windows are short.
+template <int M, bool JOIN>
+static void launch_scatter_one(const ScatterArgs &a, int nm, bool planar, hipStream_t s)
 {
-    if (planar) {  // one map per lane, one grid row per map
-        hipLaunchKernelGGL((k_adjoint_scatter<M, 1, true>), dim3(a.nblocks, nm, a.groups.n), dim3(kBlock), 0, s, a);
-        return;
-    }
-    if (nm >= 4) hipLaunchKernelGGL((k_adjoint_scatter<M, 4>), dim3(a.nblocks, nm / 4, a.groups.n), dim3(kBlock), 0, s, a);
-    if (nm & 2) {
+    const dim3 grid(a.nblocks, nm, a.groups.n), block(kBlock);
+    if (planar) hipLaunchKernelGGL((k_adjoint_scatter<M, 1, true, JOIN>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_adjoint_scatter<M, 1, false, JOIN>), grid, block, 0, s, a);
+}
+
+template <int M>
+static void launch_scatter_m(const ScatterArgs &a, int nm, bool planar, bool join, hipStream_t s)
+{
+    auto from = [&](int first) {
         ScatterArgs b = a;
-        const size_t first = (size_t)(nm & ~3);
-        b.pv += first * a.n_stride;
-        b.grad += first * a.n_stride;
-        b.rec += first * a.rec_stride;
-        b.D += first * a.d_stride;
-        hipLaunchKernelGGL((k_adjoint_scatter<M, 2>), dim3(a.nblocks, 1, a.groups.n), dim3(kBlock), 0, s, b);
+        b.pv += (size_t)first * a.n_stride;
+        b.grad += (size_t)first * a.n_stride;
+        b.rec += (size_t)first * a.rec_stride;
+        b.D += (size_t)first * a.d_stride;
+        return b;
+    };
+    const int ones = planar ? nm : nm & 1;  // planar: one map per lane, one grid row per map
+    if (!planar) {
+        constexpr int K = M <= 11 ? 4 : 2;
+        if (nm >= K)
+            hipLaunchKernelGGL((k_adjoint_scatter<M, K, false, false>), dim3(a.nblocks, nm / K, a.groups.n), dim3(kBlock),
+                               0, s, a);
+        if constexpr (K == 4)
+            if (nm & 2)
+                hipLaunchKernelGGL((k_adjoint_scatter<M, 2, false, false>), dim3(a.nblocks, 1, a.groups.n), dim3(kBlock), 0,
+                                   s, from(nm & ~3));
     }
-    if (nm & 1) {
-        ScatterArgs b = a;
-        const size_t last = (size_t)(nm - 1);
-        b.pv += last * a.n_stride;
-        b.grad += last * a.n_stride;
-        b.rec += last * a.rec_stride;
-        b.D += last * a.d_stride;
-        hipLaunchKernelGGL((k_adjoint_scatter<M, 1>), dim3(a.nblocks, 1, a.groups.n), dim3(kBlock), 0, s, b);
+    if (ones) {
+        if (join) launch_scatter_one<M, true>(from(nm - ones), ones, planar, s);
+        else launch_scatter_one<M, false>(from(nm - ones), ones, planar, s);
     }
 }
 
@@ -444,7 +494,7 @@ static z3_status adjoint_chunk_maps(z3_index idx, int map, int nm, int m_max, in
     sa.groups = bin_groups(idx, sa.nblocks);
     sa.px0 = idx->plane_x0; sa.py0 = idx->plane_y0; sa.psx = idx->plane_sx;
     switch (m_max) {
-#define Z3_CASE(MM) case MM: launch_scatter_m<MM>(sa, nm, idx->planar, s); break;
+#define Z3_CASE(MM) case MM: launch_scatter_m<MM>(sa, nm, idx->planar, short_windows(idx), s); break;
         Z3_CASE(0) Z3_CASE(1) Z3_CASE(2) Z3_CASE(3) Z3_CASE(4) Z3_CASE(5) Z3_CASE(6) Z3_CASE(7)
         Z3_CASE(8) Z3_CASE(9) Z3_CASE(10) Z3_CASE(11) Z3_CASE(12) Z3_CASE(13) Z3_CASE(14)
         Z3_CASE(15) Z3_CASE(16)

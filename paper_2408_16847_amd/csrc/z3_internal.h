@@ -160,6 +160,7 @@ struct BinGroups {
     unsigned char first[Z3_MAX_NBINS + 1];
 };
 BinGroups bin_groups(const z3_index_s *idx, int64_t nblk);
+bool short_windows(const z3_index_s *idx);  // windows of few pairs (z3_multipoles.hip)
 
 // multipole kernels (z3_multipoles.hip)
 // Pivot positions: either the index's own points (index order) or an external catalogue.

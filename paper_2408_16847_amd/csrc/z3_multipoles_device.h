@@ -480,9 +480,6 @@ void k_multipoles(MultArgs a)
     }
 }
 
-// Whether a launch over this index walks window lists (z3_multipoles.hip).
-bool short_windows(const z3_index_s *idx);
-
 // Launch over window lists (z3_multipoles_list.hip).
 z3_status launch_multipoles_list(int m_max, bool planar, bool mixed, bool self, const MultArgs &a, hipStream_t s);
 
