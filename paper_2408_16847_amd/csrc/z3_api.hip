@@ -290,8 +290,8 @@ z3_status device_block(void **p, size_t bytes, const char *what)
     }
     try {
         std::lock_guard<std::mutex> lk(g_blk_mu);
+        g_blk_idle.reserve(g_blk_live.size() + 1 + g_blk_idle.size());  // so that giving back never allocates
         g_blk_live.push_back(DevBlock{dev, *p, bytes});
-        g_blk_idle.reserve(g_blk_live.size() + g_blk_idle.size());  // so that giving back never allocates
     } catch (...) {
         (void)hipFree(*p);
         *p = nullptr;
