@@ -225,8 +225,8 @@ constexpr int kAggSlots = 1024;
 // What bounds it: the FP64 work of a pair (about 60 operations) in lanes that wait for the
 // longest window of their wave, and the latency of the records.  JOIN walks a window's two segments
 // as one, so that lanes even out over their sum: 786,000 pixels x 15 bins (m_max 10, windows of 4 pairs)
-// 3.70 -> 3.35 ms; with windows of 9 and more pairs the bookkeeping costs more than that (3 maps, 6
-// bins to 400', 21.6 -> 24.0 ms).  Several bands at a time took the gain back.  With four or two maps
+// 7.26 -> 6.92 ms a gradient; with windows of 9 and more pairs the bookkeeping costs more than that (3 maps, 6
+// bins to 400', 21.6 -> 24.0 ms a gradient).  Several bands at a time took the gain back.  With four or two maps
 // a lane the two forms are equal, and only the plain one is built.
 template <int M, int K, bool PLANAR, bool JOIN>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(adjoint_waves_per_eu<M, K>())))

@@ -486,7 +486,7 @@ static z3_status launch_pair(const PairArgs &c, bool f32, bool sym, int64_t nseg
 // 3.3 ms of MFMA, and the vector unit's split of v_p U_i costs about as much.  The tile's loads are
 // requested one tile ahead, so that they pass beside the products; an operand of 4 k-steps is one
 // 16-byte LDS read without bank conflicts instead of four scalar ones; and on the mixed path 2
-// blocks fit a CU (126 VGPRs).  With loads, barrier and products in turn it took 11.3 ms, now 6.5;
+// blocks fit a CU (126 VGPRs).  With loads, barrier and products in turn it took 11.3 ms, now 6.8;
 // FP64 16.4 -> 9.5 ms.
 constexpr int kGramWaves = 8;
 constexpr int kGramThreads = kGramWaves * 64;
