@@ -197,12 +197,13 @@ z3_status gather_pivots(const int *perm, int64_t len, Pivots piv, int64_t p0, co
                         double *gx, double *gy, double *gz, double *gv, hipStream_t s);
 
 // Many maps over one set of positions: the MFMA kernel (one block per pivot, every map at
-// once) or passes of the register-tiled kernel over the groups of kMapGroup maps.  Measured on
-// the Nside 512 map at m_max = 10 (estimator step, multipoles and contraction): a group pass
-// costs ~0.148 s (FP64) / ~0.14 s (mixed), so n maps take ~37 / ~35 ms per map; the MFMA
-// kernel takes 1.05-1.10 / 0.69-0.72 s for 5 to 16 maps, 1.39 / 0.89 s for 32, 2.06 / 1.33 s
-// for 48 and 2.15 / 1.37 s for 64.  The groups are therefore faster up to ~56 maps on the
-// FP64 path and ~24 on the mixed one.  A block shape fixed by the caller
+// once) or passes of the register-tiled kernel over the groups of kMapGroup maps.  Measured,
+// estimator calls at m_max = 10 and 15 bins, groups / MFMA in ms: 300,000 pivots of the Nside 512
+// map mixed 16 maps 47 / 75, 24 maps 71 / 88, 64 maps ~189 / 122; FP64 32 maps 95 / 141, 56 maps
+// 167 / 210, 64 maps ~191 / 191; the Nside 128 map mixed 24 maps 8.5 / 10.9, 64 maps ~22.6 / 20.6;
+// FP64 56 maps 22.0 / 25.6, 64 maps ~25 / 27.  The groups are faster up to about 28 maps on the
+// mixed path and 60 on the FP64 one; the lines stand at 24 and 56, which the interface states.
+// A block shape fixed by the caller
 // (z3_index_set_batch_shape) selects the MFMA kernel for more than kMapGroup maps.
 inline bool many_maps_on_mfma(const z3_index_s *idx, int prec)
 {
