@@ -109,7 +109,8 @@ z3_status z3_build_index(int64_t n, const double *xyz, const double *w, int nbin
  * catalogue's original order.  The index stores w_i x_i in index order and, per map,
  * 32-byte neighbour records {x, y, z, w x} (2 n records: every latitude band is stored
  * twice in a row).  Replaces values attached before, and then waits for the device's earlier
- * work, which may still read them.
+ * work, which may still read them; where the runtime refuses that wait (while a stream is being
+ * captured) the call fails with Z3_ERR_HIP and the old values stay.
  */
 z3_status z3_index_set_values(z3_index idx, int nmaps, const double *x, void *stream);
 
@@ -189,7 +190,8 @@ z3_status z3_build_index_planar(int64_t n, const double *xy, const double *w, in
 /*
  * Release an index and its device memory (NULL is ignored).  Waits for the device's work.  The
  * library keeps up to 4 GiB of such memory per device for the next index; it gives it back
- * when an allocation of its own fails.
+ * when an allocation of its own fails.  Where the runtime refuses the wait (while a stream is
+ * being captured), the memory goes to no other index until a later wait has succeeded.
  */
 void z3_index_free(z3_index idx);
 

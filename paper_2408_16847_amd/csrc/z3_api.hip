@@ -122,8 +122,6 @@ CallScope::~CallScope()
     t_scope = prev;
 }
 
-static void release_idle(int dev);
-
 z3_status scratch_alloc(void **p, size_t bytes, hipStream_t s)
 {
     *p = nullptr;
@@ -212,160 +210,6 @@ void scratch_free(void *p, hipStream_t s)
             }
     }
     (void)hipFreeAsync(p, s);
-}
-
-// ---- device blocks of the indexes -----------------------------------------------------
-// An index takes a dozen arrays and gives them back when it is freed; a program that makes an
-// index per catalogue paid hipMalloc and hipFree for each (20 of each per build: 4 + 2.6 us
-// apiece for 4,000 points, 36 + 20 us for 491,000, 158 + 51 us for 3.1e6: 4 ms of a 65 ms
-// estimate).  Blocks given back are kept for the next index, at most kIdleBytes and
-// kIdleBlocks per device, the oldest leaving first; all idle blocks are given back to the
-// runtime when an allocation fails.  A block returns here only when no work that uses it is in
-// flight on any stream, so the next owner may use it anywhere.
-struct DevBlock {
-    int dev;
-    void *p;
-    size_t bytes;
-};
-constexpr size_t kIdleBytes = (size_t)4 << 30;
-constexpr size_t kIdleBlocks = 96;
-static std::mutex g_blk_mu;
-static std::vector<DevBlock> g_blk_live, g_blk_idle;  // idle: oldest first
-
-static void release_idle(int dev)
-{
-    for (;;) {
-        void *p = nullptr;
-        {
-            std::lock_guard<std::mutex> lk(g_blk_mu);
-            for (size_t i = 0; i < g_blk_idle.size() && !p; ++i)
-                if (g_blk_idle[i].dev == dev) {
-                    p = g_blk_idle[i].p;
-                    g_blk_idle.erase(g_blk_idle.begin() + i);
-                }
-        }
-        if (!p) return;
-        (void)hipFree(p);
-    }
-}
-
-z3_status device_block(void **p, size_t bytes, const char *what)
-{
-    *p = nullptr;
-    z3_status st = alloc_allowed(bytes, what);
-    if (st != Z3_OK) return st;
-    int dev = 0;
-    if ((st = check_hip(hipGetDevice(&dev), "hipGetDevice")) != Z3_OK) return st;
-    {
-        // the smallest idle block that fits and is not wasted on a much smaller array
-        std::lock_guard<std::mutex> lk(g_blk_mu);
-        size_t best = g_blk_idle.size();
-        for (size_t i = 0; i < g_blk_idle.size(); ++i) {
-            const DevBlock &b = g_blk_idle[i];
-            if (b.dev == dev && b.bytes >= bytes && b.bytes <= 2 * bytes + 65536 &&
-                (best == g_blk_idle.size() || b.bytes < g_blk_idle[best].bytes))
-                best = i;
-        }
-        if (best < g_blk_idle.size()) {
-            const DevBlock b = g_blk_idle[best];
-            try {
-                g_blk_live.push_back(b);
-            } catch (...) {
-                return fail(Z3_ERR_OUT_OF_MEMORY, "%s: host allocation failed", what);
-            }
-            g_blk_idle.erase(g_blk_idle.begin() + best);
-            *p = b.p;
-            return Z3_OK;
-        }
-    }
-    hipError_t e = hipMalloc(p, bytes);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        release_idle(dev);
-        e = hipMalloc(p, bytes);
-    }
-    if ((st = check_hip(e, what)) != Z3_OK) {
-        *p = nullptr;
-        return st;
-    }
-    try {
-        std::lock_guard<std::mutex> lk(g_blk_mu);
-        g_blk_idle.reserve(g_blk_live.size() + 1 + g_blk_idle.size());  // so that giving back never allocates
-        g_blk_live.push_back(DevBlock{dev, *p, bytes});
-    } catch (...) {
-        (void)hipFree(*p);
-        *p = nullptr;
-        return fail(Z3_ERR_OUT_OF_MEMORY, "%s: host allocation failed", what);
-    }
-    return Z3_OK;
-}
-
-void return_block(void *p)
-{
-    if (!p) return;
-    DevBlock b{};
-    {
-        std::lock_guard<std::mutex> lk(g_blk_mu);
-        for (size_t i = 0; i < g_blk_live.size(); ++i)
-            if (g_blk_live[i].p == p) {
-                b = g_blk_live[i];
-                g_blk_live[i] = g_blk_live.back();
-                g_blk_live.pop_back();
-                break;
-            }
-        if (b.p && b.bytes <= kIdleBytes) g_blk_idle.push_back(b);
-    }
-    if (b.p && b.bytes > kIdleBytes) (void)hipFree(b.p);
-    // the oldest idle blocks leave until the rest is within bounds
-    for (;;) {
-        DevBlock old{};
-        {
-            std::lock_guard<std::mutex> lk(g_blk_mu);
-            size_t held = 0, count = 0, first = g_blk_idle.size();
-            for (size_t i = 0; i < g_blk_idle.size(); ++i)
-                if (g_blk_idle[i].dev == b.dev) {
-                    held += g_blk_idle[i].bytes;
-                    if (count++ == 0) first = i;
-                }
-            if (held <= kIdleBytes && count <= kIdleBlocks) return;
-            old = g_blk_idle[first];
-            g_blk_idle.erase(g_blk_idle.begin() + first);
-        }
-        (void)hipFree(old.p);
-    }
-}
-
-// Pinned host buffers for the sizes a build reads back, kept between builds (one per build
-// running at a time).
-constexpr size_t kPinnedIdle = 8;
-static std::mutex g_pin_mu;
-static std::vector<void *> g_pin_idle = [] { std::vector<void *> v; v.reserve(kPinnedIdle); return v; }();
-
-z3_status pinned_take(void **p)
-{
-    *p = nullptr;
-    {
-        std::lock_guard<std::mutex> lk(g_pin_mu);
-        if (!g_pin_idle.empty()) {
-            *p = g_pin_idle.back();
-            g_pin_idle.pop_back();
-            return Z3_OK;
-        }
-    }
-    return check_hip(hipHostMalloc(p, kPinnedBytes, hipHostMallocPortable), "pinned host buffer");
-}
-
-void pinned_give(void *p)
-{
-    if (!p) return;
-    {
-        std::lock_guard<std::mutex> lk(g_pin_mu);
-        if (g_pin_idle.size() < kPinnedIdle) {
-            g_pin_idle.push_back(p);
-            return;
-        }
-    }
-    (void)hipHostFree(p);
 }
 
 // ---- kernel timing -------------------------------------------------------------------

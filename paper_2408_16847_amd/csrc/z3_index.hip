@@ -525,13 +525,13 @@ static z3_status exclusive_scan(const int *in, int64_t n, int *out, int *tmp, hi
     return check_launch("k_scan_add");
 }
 
-// The index's arrays go back to the idle blocks: no work that uses them may be in flight.
-static void free_ptrs(z3_index idx)
+// The index's arrays go back to the kept blocks; `waited`: no work that uses them is in flight.
+static void free_ptrs(z3_index idx, bool waited)
 {
     void *blocks[] = {idx->d_edges, idx->d_bands, idx->d_cell_start, idx->d_x, idx->d_y, idx->d_z, idx->d_w,
                       idx->d_perm, idx->d_band, idx->d_wdbl, idx->d_permdbl, idx->d_v, idx->d_rec, idx->d_vgrp,
                       idx->d_vmat64, idx->d_vmat32};
-    for (void *p : blocks) return_block(p);
+    for (void *p : blocks) return_block(p, waited ? idx->device : -1);
     void *ps[] = {idx->cap_ws, idx->d_phi_bounds, idx->d_phi_tab};
     for (void *p : ps)
         if (p) (void)hipFree(p);
@@ -542,8 +542,7 @@ static void free_ptrs(z3_index idx)
 void free_index(z3_index idx)
 {
     (void)hipSetDevice(idx->device);
-    (void)hipDeviceSynchronize();
-    free_ptrs(idx);
+    free_ptrs(idx, wait_device(idx->device) == Z3_OK);
     delete idx;
 }
 
@@ -566,24 +565,28 @@ z3_status build_index_impl(int64_t n, const double *xyz, const double *w, int nb
     idx->nbins = nbins;
     idx->planar = planar;
     z3_status st = Z3_OK;
-    auto bail = [&](z3_status code) {
-        (void)hipStreamSynchronize(s);
-        free_ptrs(idx);
-        delete idx;
-        return code;
-    };
     // temporaries: given back on return (every path out of this function synchronises the
-    // stream first)
+    // stream first; where the runtime refuses that, they are set aside)
     struct Temps {
         void *p[10] = {};
         int count = 0;
         void *pin = nullptr;
+        int dev = 0;
+        bool waited = true;
         ~Temps()
         {
-            for (int i = 0; i < count; ++i) return_block(p[i]);
-            pinned_give(pin);
+            for (int i = 0; i < count; ++i) return_block(p[i], waited ? dev : -1);
+            pinned_give(pin, waited);
         }
     } tmp;
+    tmp.dev = idx->device;
+    auto bail = [&](z3_status code) {
+        tmp.waited = hipStreamSynchronize(s) == hipSuccess;
+        if (!tmp.waited) (void)hipGetLastError();  // `code` is what the caller sees
+        free_ptrs(idx, tmp.waited);
+        delete idx;
+        return code;
+    };
     auto temp = [&](auto **p, size_t count, const char *what) {
         const z3_status e = dalloc(p, count, what);
         if (e == Z3_OK) tmp.p[tmp.count++] = *p;
@@ -819,9 +822,9 @@ z3_status set_values_impl(z3_index idx, int nmaps, const double *x, hipStream_t 
     z3_status st;
     if (idx->d_v) {
         // earlier work, on any stream, may still read the old values
-        (void)hipDeviceSynchronize();
+        if ((st = wait_device(idx->device)) != Z3_OK) return st;
         void *old[] = {idx->d_v, idx->d_rec, idx->d_vgrp, idx->d_vmat64, idx->d_vmat32};
-        for (void *p : old) return_block(p);
+        for (void *p : old) return_block(p, idx->device);
         idx->d_v = nullptr;
         idx->d_rec = nullptr;
         idx->d_vgrp = nullptr;

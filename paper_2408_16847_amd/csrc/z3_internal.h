@@ -134,14 +134,20 @@ z3_status check_launch(const char *what);
 // Z3_ERR_OUT_OF_MEMORY if `bytes` exceed the device allocation limit (z3_set_device_alloc_limit)
 z3_status alloc_allowed(size_t bytes, const char *what);
 
-// device memory of the indexes, kept between them (z3_api.hip); a block may be returned only
-// when no work that uses it is in flight
+// device memory of the indexes, kept between them (z3_blocks.hip)
 z3_status device_block(void **p, size_t bytes, const char *what);
-void return_block(void *p);
-// a pinned host buffer of kPinnedBytes
+// Gives a block back.  waited_dev: the device whose work that uses the block the caller has waited
+// for, with success; -1 if it could not wait (the block then has no new owner until a later
+// wait_device on its device succeeds)
+void return_block(void *p, int waited_dev);
+// Waits for all work on a device
+z3_status wait_device(int dev);
+// All idle blocks of a device back to the runtime
+void release_idle(int dev);
+// a pinned host buffer of kPinnedBytes; waited: no copy into it is in flight
 constexpr size_t kPinnedBytes = 32768;
 z3_status pinned_take(void **p);
-void pinned_give(void *p);
+void pinned_give(void *p, bool waited);
 
 // index kernels (z3_index.hip)
 z3_status build_index_impl(int64_t n, const double *xyz, const double *w, int nbins,
