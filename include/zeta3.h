@@ -108,9 +108,10 @@ z3_status z3_build_index(int64_t n, const double *xyz, const double *w, int nbin
  * Attach field values: nmaps maps of n values each, x [nmaps][n] FP64 in the
  * catalogue's original order.  The index stores w_i x_i in index order and, per map,
  * 32-byte neighbour records {x, y, z, w x} (2 n records: every latitude band is stored
- * twice in a row).  Replaces values attached before, and then waits for the device's earlier
- * work, which may still read them; where the runtime refuses that wait (while a stream is being
- * captured) the call fails with Z3_ERR_HIP and the old values stay.
+ * twice in a row).  Waits for earlier work on `stream`; replaces values attached before, and then
+ * waits for the device's earlier work on every stream, which may still read them.  Where the
+ * runtime refuses the wait (while a stream is being captured) the call fails with Z3_ERR_HIP and
+ * values attached before stay.
  */
 z3_status z3_index_set_values(z3_index idx, int nmaps, const double *x, void *stream);
 

@@ -820,7 +820,9 @@ z3_status update_values_impl(z3_index idx, const double *x, hipStream_t s)
 z3_status set_values_impl(z3_index idx, int nmaps, const double *x, hipStream_t s)
 {
     z3_status st;
-    if (idx->d_v) {
+    if (!idx->d_v) {
+        if ((st = check_hip(hipStreamSynchronize(s), "hipStreamSynchronize")) != Z3_OK) return st;
+    } else {
         // earlier work, on any stream, may still read the old values
         if ((st = wait_device(idx->device)) != Z3_OK) return st;
         void *old[] = {idx->d_v, idx->d_rec, idx->d_vgrp, idx->d_vmat64, idx->d_vmat32};
