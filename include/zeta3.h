@@ -447,7 +447,9 @@ z3_status z3_resum(int m_max, int nbins, const double *zeta, int nphi, const dou
  *            from its stream-ordered pool (at most 1 GiB; the call cannot then be captured
  *            into a graph).  z3_fftlog_workspace_size gives the bytes for a number of models
  *            per pass; a smaller workspace processes fewer models per pass (Z3_ERR_INVALID_ARG
- *            if it holds none).
+ *            if it holds none), and a pass takes at most 21,845 models with fewer than 2^31
+ *            samples F of the three functions.  Z3_ERR_OVERFLOW for nchi x (N + 1, rounded up to
+ *            16) of 2^31 or more.
  * Since eta_s is linear in s, A_{s1 s2} depends on s1 + s2 only: the library forms its
  * 2N + 1 distinct entries h(s1 + s2) (one product over chi for all models) and never the
  * (N+1)^2 matrix; since P is real, the terms (s1, s2) and (-s1, -s2) are conjugate and only

@@ -7,6 +7,7 @@
 #include <mutex>
 #include <vector>
 
+#include "z3_fftlog_pass.h"
 #include "z3_internal.h"
 
 namespace z3 {
@@ -1226,11 +1227,12 @@ Z3_API z3_status z3_fftlog_a_functions(int N, const double *Pk, double k_min, do
     if (nmodels == 0) return Z3_OK;
     if (!Pk || !F || !theta || !out) return fail(Z3_ERR_INVALID_ARG, "z3_fftlog_a_functions: NULL pointer");
     const hipStream_t s = as_stream(stream);
-    int chunk = nmodels < 21845 ? nmodels : 21845;  // one grid z index per factor pair and model of a pass
+    if (fftlog_most_models(N, nchi) < 1)
+        return fail(Z3_ERR_OVERFLOW, "z3_fftlog_a_functions: %d chi samples at N = %d", nchi, N);
     if (workspace) {
         if (reinterpret_cast<uintptr_t>(workspace) % 256)
             return fail(Z3_ERR_INVALID_ARG, "z3_fftlog_a_functions: workspace not 256-byte aligned");
-        while (chunk > 1 && fftlog_workspace_bytes(N, nchi, ntheta, chunk) > workspace_bytes) chunk = (chunk + 1) / 2;
+        const int chunk = fftlog_pass_models(N, nchi, ntheta, nmodels, workspace_bytes);
         if (fftlog_workspace_bytes(N, nchi, ntheta, chunk) > workspace_bytes)
             return fail(Z3_ERR_INVALID_ARG, "z3_fftlog_a_functions: workspace of %zu bytes holds no model (%zu needed)",
                         workspace_bytes, fftlog_workspace_bytes(N, nchi, ntheta, 1));
@@ -1239,7 +1241,7 @@ Z3_API z3_status z3_fftlog_a_functions(int N, const double *Pk, double k_min, do
     }
     CallScope scope(nullptr, s);
     const size_t kMaxAuto = (size_t)1 << 30;
-    while (chunk > 1 && fftlog_workspace_bytes(N, nchi, ntheta, chunk) > kMaxAuto) chunk = (chunk + 1) / 2;
+    const int chunk = fftlog_pass_models(N, nchi, ntheta, nmodels, kMaxAuto);
     void *ws = nullptr;
     z3_status st = scratch_alloc(&ws, fftlog_workspace_bytes(N, nchi, ntheta, chunk), s);
     if (st != Z3_OK) return st;

@@ -31,6 +31,7 @@
 // wave per coefficient; the operands are elementwise kernels.
 #include <type_traits>
 
+#include "z3_fftlog_pass.h"
 #include "z3_internal.h"
 
 namespace z3 {
@@ -257,8 +258,8 @@ __global__ __launch_bounds__(256) void k_cgemm(CGemm g)
     const int jb = j0 + r;
     const bool jin = jb < g.N;
 
-    // per-lane row pointers of A and column pointer of B; k offsets stay 32-bit (k a_k, k b_k
-    // < 2^31 for every product launched).  Rows and columns past the matrix read its first ones
+    // per-lane row pointers of A and column pointer of B; k offsets stay 32-bit (k a_k and k b_k
+    // < 2^31, see fftlog_most_models).  Rows and columns past the matrix read its first ones
     // and are not stored, so only the last k-step, past K, is masked: a zero B with the A of K - 1
     const double2 *Ar[RM];
 #pragma unroll
@@ -402,25 +403,6 @@ __global__ void k_fftlog_out(const double *I1, int T, int nmodels, double *out)
     const int ij = (int)(t % per), i = ij / T, j = ij % T;
     const double *Ib = I1 + (size_t)b * per;
     out[(size_t)(3 * b + 1) * per + ij] = Ib[ij] + Ib[(size_t)j * T + i];
-}
-
-struct FftlogLayout {
-    size_t ld, ldw, ldh, ldt;
-};
-
-static FftlogLayout fftlog_layout(int N)
-{
-    auto up16 = [](size_t v) { return (v + 15) / 16 * 16; };
-    return FftlogLayout{up16((size_t)N + 1), up16((size_t)N / 2 + 1), up16((size_t)N + 1), up16(2 * (size_t)N + 1)};
-}
-
-size_t fftlog_workspace_bytes(int N, int nchi, int T, int chunk)
-{
-    // nine pieces, each rounded up to 256 bytes by the carving in fftlog_impl
-    const FftlogLayout L = fftlog_layout(N);
-    return sizeof(double2) * (8 * L.ld + 4 * (size_t)T * (L.ld + L.ldw) + (size_t)nchi * L.ldh +
-                              (size_t)chunk * 3 * (L.ldt + (size_t)T * L.ld)) +
-           sizeof(double) * (size_t)chunk * 3 * (nchi + (size_t)T * T) + 9 * 256;
 }
 
 z3_status fftlog_impl(int N, const double *Pk, double k_min, double k_max, const double *nu, int nchi, double chi_min,
