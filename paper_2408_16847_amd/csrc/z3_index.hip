@@ -247,29 +247,35 @@ static z3_status launch_band_of_point(const double *xyz, int64_t n, const BandRu
 }
 
 // The band table from the counts and colatitude ranges, and [2]: number of cells, largest
-// count.  One block walks the bands 1024 at a time with running offsets.
+// count.  One block walks the bands 1024 at a time with running offsets.  At most 4 (2^29 - 1)
+// + 2^26 cells: their number is exact in 32 unsigned bits, also where it is too large for the table.
 constexpr int kTableThreads = 1024;
 __global__ __launch_bounds__(kTableThreads) void k_band_table(int nbands, double h, const int *count, const double *band_th,
-                                                             Band *bands, int *stats)
+                                                             Band *bands, uint32_t *stats)
 {
-    __shared__ int wpts[kTableThreads / kWave], wcells[kTableThreads / kWave], wmax[kTableThreads / kWave];
+    __shared__ int wpts[kTableThreads / kWave], wmax[kTableThreads / kWave];
+    __shared__ uint32_t wcells[kTableThreads / kWave];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    int pt0 = 0, cell0 = 0, most = 0;  // of the bands before this round
+    int pt0 = 0, most = 0;  // of the bands before this round
+    uint32_t cell0 = 0;
     for (int k0 = 0; k0 < nbands; k0 += kTableThreads) {
         const int k = k0 + (int)threadIdx.x;
         const int npts = k < nbands ? count[k] : 0;
         const int ncell = k < nbands ? max(1, kCellsPerPoint * npts) : 0;
-        int p = npts, c = ncell, mx = npts;
+        int p = npts, mx = npts;
+        uint32_t c = (uint32_t)ncell;
 #pragma unroll
         for (int o = 1; o < kWave; o <<= 1) {
-            const int tp = __shfl_up(p, o, kWave), tc = __shfl_up(c, o, kWave);
+            const int tp = __shfl_up(p, o, kWave);
+            const uint32_t tc = __shfl_up(c, o, kWave);
             if (lane >= o) { p += tp; c += tc; }
             mx = max(mx, __shfl_xor(mx, o, kWave));
         }
         __syncthreads();  // the previous round's wave sums are read
         if (lane == kWave - 1) { wpts[wave] = p; wcells[wave] = c; wmax[wave] = mx; }
         __syncthreads();
-        int pb = pt0 + p - npts, cb = cell0 + c - ncell;
+        int pb = pt0 + p - npts;
+        uint32_t cb = cell0 + c - (uint32_t)ncell;
         for (int w = 0; w < kTableThreads / kWave; ++w) {
             if (w < wave) { pb += wpts[w]; cb += wcells[w]; }
             pt0 += wpts[w];
@@ -281,7 +287,7 @@ __global__ __launch_bounds__(kTableThreads) void k_band_table(int nbands, double
             b.npts = npts;
             b.pt_start = pb;
             b.ncell = ncell;
-            b.cell_off = cb;
+            b.cell_off = (int)cb;
             b.cells_per_rad = (float)((double)ncell / kTwoPi);
             const double lo = npts ? band_th[2 * (int64_t)k] : k * h, hi = npts ? band_th[2 * (int64_t)k + 1] : k * h;
             b.th_lo = lo;
@@ -297,7 +303,7 @@ __global__ __launch_bounds__(kTableThreads) void k_band_table(int nbands, double
             bands[k] = b;
         }
     }
-    if (threadIdx.x == 0) { stats[0] = cell0; stats[1] = most; }
+    if (threadIdx.x == 0) { stats[0] = cell0; stats[1] = (uint32_t)most; }
 }
 
 __global__ void k_cell_of_point(int64_t n, const int *band, const double *phi, const Band *bands,
@@ -717,43 +723,64 @@ z3_status build_index_impl(int64_t n, const double *xyz, const double *w, int nb
     idx->nbands = nbands;
 
     // ---- bands -------------------------------------------------------------------------
-    // At most 4 n + nbands cells (a band without points has one); the scan below also covers the
-    // entry after the last cell, which holds n.
-    const int64_t cells_max = (int64_t)kCellsPerPoint * n + nbands;
-    if (2 * n >= (int64_t)0x7fffffff) return bail(fail(Z3_ERR_OVERFLOW, "z3_build_index: too many points or cells"));
     int *d_band = nullptr, *d_band_count = nullptr, *d_cell = nullptr, *d_cell_count = nullptr, *d_scan = nullptr;
-    int *d_stats = nullptr;
+    uint32_t *d_stats = nullptr;
     double *d_phi = nullptr, *d_band_th = nullptr;
     if ((st = temp(&d_band, n, "alloc band")) != Z3_OK) return bail(st);
     if ((st = temp(&d_phi, n, "alloc phi")) != Z3_OK) return bail(st);
     if ((st = temp(&d_band_count, (size_t)nbands + 2, "alloc band count")) != Z3_OK) return bail(st);
     if ((st = temp(&d_band_th, 2 * (size_t)nbands, "alloc band theta")) != Z3_OK) return bail(st);
-    if ((st = temp(&d_cell, n, "alloc cell")) != Z3_OK) return bail(st);
-    if ((st = temp(&d_cell_count, cells_max + 1, "alloc cell count")) != Z3_OK) return bail(st);
-    if ((st = temp(&d_scan, scan_ints(cells_max + 1), "scan alloc")) != Z3_OK) return bail(st);
     if ((st = dalloc(&idx->d_bands, nbands, "alloc bands")) != Z3_OK) return bail(st);
-    if ((st = dalloc(&idx->d_cell_start, cells_max + 1, "alloc cell start")) != Z3_OK) return bail(st);
-    d_stats = d_band_count + nbands;
-    hipLaunchKernelGGL(k_clear_counts, dim3(std::min(grid_for(std::max<int64_t>(cells_max + 1, nbands)), 8192u)), dim3(256),
-                       0, s, d_band_count, d_band_th, nbands, planar ? INFINITY : 4.0, d_cell_count, cells_max + 1);
-    const BandRule rule{1.0 / h, idx->plane_x0, idx->plane_y0, idx->plane_sx, planar ? INFINITY : 4.0, nbands};
+    d_stats = reinterpret_cast<uint32_t *>(d_band_count + nbands);
+    // The table's totals are read back at the end.  They are read before there is any cell array
+    // where they may say that the catalogue is refused (a band of more than 2^26 points, 2^31
+    // cells), and where the arrays for the most cells there can be are not to be had.
+    int64_t cells = (int64_t)kCellsPerPoint * n + nbands;  // a band without points has one
+    bool known = 64 * n > (int64_t)UINT32_MAX || cells >= (int64_t)0x7fffffff;
+    const double lo0 = planar ? INFINITY : 4.0;
+    // (the scan also covers the entry after the last cell, which holds n)
+    auto cell_arrays = [&]() {
+        z3_status e = Z3_OK;
+        if (!d_cell) e = temp(&d_cell, n, "alloc cell");
+        if (e == Z3_OK && !d_cell_count) e = temp(&d_cell_count, cells + 1, "alloc cell count");
+        if (e == Z3_OK && !d_scan) e = temp(&d_scan, scan_ints(cells + 1), "scan alloc");
+        if (e == Z3_OK && !idx->d_cell_start) e = dalloc(&idx->d_cell_start, cells + 1, "alloc cell start");
+        return e;
+    };
+    auto clear_counts = [&](int bands, int64_t ncells) {
+        const int64_t len = std::max<int64_t>(ncells, bands);
+        hipLaunchKernelGGL(k_clear_counts, dim3(std::min(grid_for(len), 8192u)), dim3(256), 0, s, d_band_count, d_band_th,
+                           bands, lo0, d_cell_count, ncells);
+        return check_launch("k_clear_counts");
+    };
+    if (!known) {
+        st = cell_arrays();
+        if (st != Z3_OK && st != Z3_ERR_OUT_OF_MEMORY) return bail(st);
+        known = st != Z3_OK;
+    }
+    if ((st = clear_counts(nbands, known ? 0 : cells + 1)) != Z3_OK) return bail(st);
+    const BandRule rule{1.0 / h, idx->plane_x0, idx->plane_y0, idx->plane_sx, lo0, nbands};
     st = planar ? launch_band_of_point<true>(xyz, n, rule, d_band, d_phi, d_band_count, d_band_th, s)
                 : launch_band_of_point<false>(xyz, n, rule, d_band, d_phi, d_band_count, d_band_th, s);
     if (st != Z3_OK) return bail(st);
     hipLaunchKernelGGL(k_band_table, dim3(1), dim3(kTableThreads), 0, s, nbands, h, d_band_count, d_band_th,
                        idx->d_bands, d_stats);
     if ((st = check_launch("k_band_table")) != Z3_OK) return bail(st);
-    const int *stats = static_cast<const int *>(tmp.pin);
+    const uint32_t *stats = static_cast<const uint32_t *>(tmp.pin);
     auto read_stats = [&]() {
-        z3_status e = check_hip(hipMemcpyAsync(tmp.pin, d_stats, 2 * sizeof(int), hipMemcpyDeviceToHost, s), "copy");
+        z3_status e = check_hip(hipMemcpyAsync(tmp.pin, d_stats, 2 * sizeof(uint32_t), hipMemcpyDeviceToHost, s), "copy");
         return e == Z3_OK ? check_hip(hipStreamSynchronize(s), "sync") : e;
     };
-    if (cells_max >= (int64_t)0x7fffffff) {
-        // near the range's end: the exact number of cells decides (the table's count of them
-        // wraps below zero when it is beyond), before any kernel indexes them
+    if (known) {
         if ((st = read_stats()) != Z3_OK) return bail(st);
-        if (stats[0] < 0 || stats[0] == 0x7fffffff)
-            return bail(fail(Z3_ERR_OVERFLOW, "z3_build_index: too many points or cells"));
+        // the multipole kernel addresses a band's doubled records (64 B per point) with 32-bit
+        // byte offsets
+        if ((int64_t)stats[1] * 64 > (int64_t)UINT32_MAX)
+            return bail(fail(Z3_ERR_UNSUPPORTED, "z3_build_index: %u points in one latitude band", stats[1]));
+        if (stats[0] >= 0x7fffffffu) return bail(fail(Z3_ERR_OVERFLOW, "z3_build_index: too many points or cells"));
+        cells = stats[0];
+        if ((st = cell_arrays()) != Z3_OK) return bail(st);
+        if ((st = clear_counts(0, cells + 1)) != Z3_OK) return bail(st);
     }
 
     // ---- cells, sort -----------------------------------------------------------------------
@@ -769,11 +796,11 @@ z3_status build_index_impl(int64_t n, const double *xyz, const double *w, int nb
     if (n > 0)
         hipLaunchKernelGGL(k_cell_of_point, dim3(grid_for(n)), dim3(256), 0, s, n, d_band, d_phi, idx->d_bands,
                            d_cell, d_cell_count);
-    if ((st = exclusive_scan(d_cell_count, cells_max + 1, idx->d_cell_start, d_scan, s)) != Z3_OK) return bail(st);
+    if ((st = exclusive_scan(d_cell_count, cells + 1, idx->d_cell_start, d_scan, s)) != Z3_OK) return bail(st);
     if (n > 0) {
         hipLaunchKernelGGL(k_scatter, dim3(grid_for(n)), dim3(256), 0, s, n, d_cell, idx->d_cell_start,
                            d_cell_count, idx->d_perm);
-        hipLaunchKernelGGL(k_sort_cells, dim3(grid_for(cells_max)), dim3(256), 0, s, cells_max, idx->d_cell_start,
+        hipLaunchKernelGGL(k_sort_cells, dim3(grid_for(cells)), dim3(256), 0, s, cells, idx->d_cell_start,
                            idx->d_perm);
         hipLaunchKernelGGL(k_gather_points, dim3(grid_for(n)), dim3(256), 0, s, n, idx->d_perm, xyz, w, d_band,
                            idx->d_bands, idx->d_x, idx->d_y, idx->d_z, idx->d_w, idx->d_band, idx->d_permdbl,
@@ -782,10 +809,6 @@ z3_status build_index_impl(int64_t n, const double *xyz, const double *w, int nb
     if ((st = check_launch("k_gather_points")) != Z3_OK) return bail(st);
     if ((st = read_stats()) != Z3_OK) return bail(st);
     idx->ncells = stats[0];
-    // the multipole kernel addresses a band's doubled records (64 B per point) with 32-bit
-    // byte offsets
-    if ((int64_t)stats[1] * 64 > (int64_t)UINT32_MAX)
-        return bail(fail(Z3_ERR_UNSUPPORTED, "z3_build_index: %d points in one latitude band", stats[1]));
     *out = idx;
     return Z3_OK;
 }
