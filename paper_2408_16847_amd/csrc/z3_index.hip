@@ -358,13 +358,17 @@ __global__ void k_plane_xyz(const double *xy, int64_t n, double *xyz)
     xyz[2 * n + i] = 0.0;
 }
 
-// The points of every cell, in any order (counting the cell's count back down).
+// The points of every cell, from its first entry on in the order of the atomics (counting the cell's
+// count back down), which is near the original one.  k_sort_cells moves each point past the later
+// ones before it: from the last entry on, the points of a crowded cell come in about the reverse
+// order and all pass each other (1,000 stacks of 300 points, one of each in turn: index and
+// values 6.5 ms so, 2.8 ms this way).
 __global__ void k_scatter(int64_t n, const int *cell, const int *cell_start, int *cell_count, int *order)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     int c = cell[i];
-    int pos = cell_start[c] + atomicSub(&cell_count[c], 1) - 1;
+    int pos = cell_start[c + 1] - atomicSub(&cell_count[c], 1);
     order[pos] = (int)i;
 }
 

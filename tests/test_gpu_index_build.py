@@ -103,3 +103,17 @@ def test_made_and_freed_on_streams_and_threads():
     for t in threads:
         t.join()
     assert not bad
+
+
+@pytest.mark.parametrize("turn", [False, True])
+def test_crowded_cells(turn):
+    # stacks of 300 points at 50 positions, one stack after the other or one point of each in turn
+    G.say("case: index build, stacks", turn)
+    base = cap_points(50, 9.0, seed=6).numpy()
+    xyz = np.ascontiguousarray(np.tile(base, (1, 300)) if turn else np.repeat(base, 300, axis=1))
+    idx = G.build(xyz, np.ones(xyz.shape[1]), E, cell_size=0.05)
+    th = np.arctan2(np.sqrt(xyz[0] ** 2 + xyz[1] ** 2), xyz[2])
+    phi = np.arctan2(xyz[1], xyz[0])
+    band = np.minimum((th * (1.0 / 0.05)).astype(np.int64), math.ceil(math.pi / 0.05) - 1)
+    assert np.array_equal(G.perm(idx), _order(band, np.where(phi < 0, phi + 2 * math.pi, phi)))
+    idx.free()
