@@ -427,6 +427,17 @@ Z3_API z3_status z3_accumulate_multipoles(z3_index idx, int map, int m_max, int 
                              p1 - p0, W, counts, idhash, pair_total, as_stream(stream));
 }
 
+// Scratch for the partial sums of a contraction: want.want bytes or, where an allocation limit, the
+// device or a capture's reservation has no room for them, want.least.  A call takes it after its other
+// scratch, so that a reservation is never short for that.
+static z3_status scratch_partials(void **p, size_t *bytes, const PartialBytes &want, hipStream_t s)
+{
+    z3_status st = scratch_alloc(p, *bytes = want.want, s);
+    if ((st == Z3_ERR_OUT_OF_MEMORY || st == Z3_ERR_INVALID_ARG) && want.least < want.want)
+        st = scratch_alloc(p, *bytes = want.least, s);
+    return st;
+}
+
 Z3_API z3_status z3_contract(int64_t npiv, int m_max, int nbins, int prec, const void *A,
                              const double *piv_v, double *zeta, void *stream)
 {
@@ -439,9 +450,9 @@ Z3_API z3_status z3_contract(int64_t npiv, int m_max, int nbins, int prec, const
     if (!zeta) return fail(Z3_ERR_INVALID_ARG, "z3_contract: zeta is NULL");
     if (npiv == 0) return Z3_OK;
     if (!A || !piv_v) return fail(Z3_ERR_INVALID_ARG, "z3_contract: A or piv_v is NULL");
-    size_t pb = contract_partial_bytes(npiv, m_max, nbins);
+    size_t pb = 0;
     void *part = nullptr;
-    z3_status st = scratch_alloc(&part, pb, as_stream(stream));
+    z3_status st = scratch_partials(&part, &pb, contract_partial_bytes(npiv, m_max, nbins), as_stream(stream));
     if (st != Z3_OK) return st;
     st = launch_contract(npiv, m_max, nbins, prec, A, npiv, piv_v, zeta, part, pb, as_stream(stream));
     scratch_free(part, as_stream(stream));
@@ -580,7 +591,7 @@ static z3_status estimate_chunks(z3_index idx, int map, int m_max, int prec, boo
     auto round256 = [](size_t b) { return (b + 255) / 256 * 256; };
     auto bytes_for = [&](int64_t c, size_t *ab, size_t *pb, size_t *sb) {
         *ab = (size_t)c * per_piv;
-        *pb = contract_partial_bytes(c, m_max, idx->nbins);
+        *pb = contract_partial_bytes(c, m_max, idx->nbins).want;
         *sb = no_self ? (size_t)((c + kWave - 1) / kWave) * idx->nbins * sizeof(double) : 0;
         return round256(*ab) + round256(*pb) + round256(*sb);
     };
@@ -606,8 +617,8 @@ static z3_status estimate_chunks(z3_index idx, int map, int m_max, int prec, boo
         wsf = no_self ? base + round256(abytes) + round256(pbytes) : nullptr;
     } else {
         if ((st = scratch_alloc(&wa, abytes, s)) != Z3_OK) return st;
-        st = scratch_alloc(&wp, pbytes, s);
-        if (st == Z3_OK && no_self) st = scratch_alloc(&wsf, sbytes, s);
+        if (no_self) st = scratch_alloc(&wsf, sbytes, s);
+        if (st == Z3_OK) st = scratch_partials(&wp, &pbytes, contract_partial_bytes(chunk, m_max, idx->nbins), s);
     }
     const double *v = idx->d_v + (size_t)map * idx->n;
     double *self_part = static_cast<double *>(wsf);
@@ -730,10 +741,10 @@ Z3_API z3_status z3_estimate_histogram(z3_index idx, int map, int m_max, int pre
     int64_t chunk = chunk_pivots(idx, m_max, sprec);
     if (chunk > p1 - p0) chunk = ((p1 - p0 + kBlock - 1) / kBlock) * kBlock;
     const size_t abytes = (size_t)chunk * (size_t)(m_max + 1) * 2 * idx->nbins * sizeof(double);
-    const size_t pbytes = contract_partial_bytes(chunk, m_max, idx->nbins);
+    size_t pbytes = 0;
     void *wa = nullptr, *wp = nullptr;
     if ((st = scratch_alloc(&wa, abytes, s)) != Z3_OK) return st;
-    st = scratch_alloc(&wp, pbytes, s);
+    st = scratch_partials(&wp, &pbytes, contract_partial_bytes(chunk, m_max, idx->nbins), s);
     const double *v = idx->d_v + (size_t)map * idx->n;
     for (int64_t c0 = p0; c0 < p1 && st == Z3_OK; c0 += chunk) {
         const int64_t c1 = c0 + chunk < p1 ? c0 + chunk : p1;
@@ -839,10 +850,10 @@ Z3_API z3_status z3_estimate_cross(z3_index idx, int map_a, int map_b, int map_c
     if (chunk > p1 - p0) chunk = ((p1 - p0 + kBlock - 1) / kBlock) * kBlock;
     const size_t elem = prec == Z3_PREC_FP64 ? 8 : 4;
     const size_t slot_elems = (size_t)chunk * (size_t)(m_max + 1) * 2 * idx->nbins;
-    const size_t pbytes = cross_partial_bytes(chunk, m_max, idx->nbins);
+    size_t pbytes = 0;
     void *wa = nullptr, *wp = nullptr;
     if ((st = scratch_alloc(&wa, slot_elems * elem * nslots, s)) != Z3_OK) return st;
-    st = scratch_alloc(&wp, pbytes, s);
+    st = scratch_partials(&wp, &pbytes, cross_partial_bytes(chunk, m_max, idx->nbins), s);
     for (int64_t c0 = p0; c0 < p1 && st == Z3_OK; c0 += chunk) {
         const int64_t c1 = c0 + chunk < p1 ? c0 + chunk : p1;
         if (grouped)
@@ -915,10 +926,9 @@ Z3_API z3_status z3_estimate_cross_catalogues(z3_index idx_b, int map_b, z3_inde
     if (chunk > p1 - p0) chunk = ((p1 - p0 + kBlock - 1) / kBlock) * kBlock;
     const size_t elem = prec == Z3_PREC_FP64 ? 8 : 4;
     const size_t slot_bytes = (size_t)chunk * (size_t)(m_max + 1) * 2 * nb * elem;
-    const size_t pbytes = cross_partial_bytes(chunk, m_max, nb);
+    size_t pbytes = 0;
     void *wa = nullptr, *wp = nullptr, *wz = nullptr, *wg = nullptr;
     if ((st = scratch_alloc(&wa, 2 * slot_bytes, s)) != Z3_OK) return st;
-    st = scratch_alloc(&wp, pbytes, s);
     // plane: pivots are [2][npiv] (x, y); a zero row stands for z
     if (st == Z3_OK && idx_b->planar) st = scratch_alloc(&wz, (size_t)npiv * sizeof(double), s);
     if (st == Z3_OK && idx_b->planar) st = launch_fill(static_cast<double *>(wz), npiv, 0.0, s);
@@ -928,6 +938,7 @@ Z3_API z3_status z3_estimate_cross_catalogues(z3_index idx_b, int map_b, z3_inde
     void *wperm = nullptr;
     if (st == Z3_OK) st = scratch_alloc(&wg, (size_t)4 * chunk * sizeof(double), s);
     if (st == Z3_OK) st = scratch_alloc(&wperm, (size_t)(p1 - p0) * sizeof(int), s);
+    if (st == Z3_OK) st = scratch_partials(&wp, &pbytes, cross_partial_bytes(chunk, m_max, nb), s);
     if (st == Z3_OK) st = sort_pivots(idx_b, piv, p0, p1 - p0, static_cast<int *>(wperm), s);
     double *gx = static_cast<double *>(wg), *gy = gx + chunk, *gz = gy + chunk, *gv = gz + chunk;
     for (int64_t c0 = p0; c0 < p1 && st == Z3_OK; c0 += chunk) {
@@ -988,11 +999,12 @@ Z3_API z3_status z3_estimate_maps(z3_index idx, int m_max, int prec, int64_t p0,
         chunk = (chunk / kBlock) * kBlock;
         if (chunk < 4 * kBlock) chunk = 4 * kBlock;
         if (chunk > p1 - p0) chunk = p1 - p0;
-        const size_t pbytes = contract_partial_bytes(chunk, m_max, idx->nbins, idx->nmaps);
+        size_t pbytes = 0;
         void *wa = nullptr, *wst = nullptr, *wp = nullptr;
         st = scratch_alloc(&wst, (size_t)idx->nmaps * chunk * per_map_piv, s);
         if (st == Z3_OK && !direct) st = scratch_alloc(&wa, (size_t)idx->nmaps * chunk * per_map_piv, s);
-        if (st == Z3_OK) st = scratch_alloc(&wp, pbytes, s);
+        if (st == Z3_OK)
+            st = scratch_partials(&wp, &pbytes, contract_partial_bytes(chunk, m_max, idx->nbins, idx->nmaps), s);
         for (int64_t c0 = p0; c0 < p1 && st == Z3_OK; c0 += chunk) {
             const int64_t c1 = c0 + chunk < p1 ? c0 + chunk : p1;
             const size_t stride = (size_t)(c1 - c0) * (m_max + 1) * 2 * idx->nbins;
@@ -1016,10 +1028,10 @@ Z3_API z3_status z3_estimate_maps(z3_index idx, int m_max, int prec, int64_t p0,
     if (chunk < 16 * kBlock) chunk = 16 * kBlock;
     if (chunk > p1 - p0) chunk = ((p1 - p0 + kBlock - 1) / kBlock) * kBlock;
     const size_t map_stride = (size_t)chunk * (m_max + 1) * 2 * idx->nbins;  // elements
-    size_t pbytes = contract_partial_bytes(chunk, m_max, idx->nbins, kMapGroup);
+    size_t pbytes = 0;
     void *wa = nullptr, *wp = nullptr;
     if ((st = scratch_alloc(&wa, (size_t)kMapGroup * chunk * per_map_piv, s)) != Z3_OK) return st;
-    if ((st = scratch_alloc(&wp, pbytes, s)) != Z3_OK) {
+    if ((st = scratch_partials(&wp, &pbytes, contract_partial_bytes(chunk, m_max, idx->nbins, kMapGroup), s)) != Z3_OK) {
         scratch_free(wa, s);
         return st;
     }
@@ -1084,10 +1096,9 @@ Z3_API z3_status z3_estimate_pivots(z3_index idx, int map, int64_t npiv, const d
     if (chunk > p1 - p0) chunk = ((p1 - p0 + kBlock - 1) / kBlock) * kBlock;
     size_t elem = prec == Z3_PREC_FP64 ? 8 : 4;
     size_t abytes = (size_t)chunk * (size_t)(m_max + 1) * 2 * idx->nbins * elem;
-    size_t pbytes = contract_partial_bytes(chunk, m_max, idx->nbins);
+    size_t pbytes = 0;
     void *wa = nullptr, *wp = nullptr, *wz = nullptr, *wg = nullptr;
     if ((st = scratch_alloc(&wa, abytes, s)) != Z3_OK) return st;
-    st = scratch_alloc(&wp, pbytes, s);
     // plane: pivots are [2][npiv] (x, y); a zero row stands for z
     if (st == Z3_OK && idx->planar) st = scratch_alloc(&wz, (size_t)npiv * sizeof(double), s);
     if (st == Z3_OK && idx->planar) st = launch_fill(static_cast<double *>(wz), npiv, 0.0, s);
@@ -1098,6 +1109,7 @@ Z3_API z3_status z3_estimate_pivots(z3_index idx, int map, int64_t npiv, const d
     void *wperm = nullptr;
     if (st == Z3_OK) st = scratch_alloc(&wg, (size_t)4 * chunk * sizeof(double), s);
     if (st == Z3_OK) st = scratch_alloc(&wperm, (size_t)(p1 - p0) * sizeof(int), s);
+    if (st == Z3_OK) st = scratch_partials(&wp, &pbytes, contract_partial_bytes(chunk, m_max, idx->nbins), s);
     if (st == Z3_OK) st = sort_pivots(idx, piv, p0, p1 - p0, static_cast<int *>(wperm), s);
     double *gx = static_cast<double *>(wg), *gy = gx + chunk, *gz = gy + chunk, *gv = gz + chunk;
     for (int64_t c0 = p0; c0 < p1 && st == Z3_OK; c0 += chunk) {

@@ -34,27 +34,40 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 static inline int tiles_for(int nbins) { return (2 * nbins + 15) / 16; }
 
 // Pivots per segment for npiv pivots and `units` (map, m, tile pair) per segment: a multiple of
-// kSegMin.
-static int segment_pivots(int64_t npiv, int64_t units)
+// kSegMin, with partial sums that fit `bytes` (at least least_bytes).
+static int segment_pivots(int64_t npiv, int64_t units, size_t bytes)
 {
-    const int64_t most = std::max<int64_t>(1, kContractUnits / units);  // segments the bound allows
+    const int64_t room = (int64_t)std::min<size_t>(kContractUnits, bytes / (256 * sizeof(double)));
+    const int64_t most = std::max<int64_t>(1, room / units);  // segments the bounds allow
     const int64_t len = (npiv + most - 1) / most;
     return (int)std::min<int64_t>(kSeg, (len + kSegMin - 1) / kSegMin * kSegMin);
 }
 
-// Partial sums (segment, unit) of any call with up to npiv pivots and up to `units` per segment
-// (a call's last chunk is shorter, its last group of maps smaller).
-static size_t most_partials(int64_t npiv, int64_t units)
+// Bytes of the partial sums (segment, unit) of any call with up to npiv pivots and up to `units`
+// per segment (a call's last chunk is shorter, its last group of maps smaller): what the shorter
+// segments above take, and the least that a call works with, in segments of kSeg.
+static size_t least_bytes(int64_t npiv, int64_t units)
 {
-    const int64_t longest = (npiv + kSeg - 1) / kSeg, shortest = (npiv + kSegMin - 1) / kSegMin;
-    const int64_t n = std::max(longest * units, std::min(shortest * units, std::max<int64_t>(kContractUnits, units)));
-    return (size_t)std::max(n, units);
+    return (size_t)(std::max<int64_t>(1, (npiv + kSeg - 1) / kSeg) * units) * 256 * sizeof(double);
 }
 
-size_t contract_partial_bytes(int64_t npiv, int m_max, int nbins, int nmaps)
+static PartialBytes partial_bytes(int64_t npiv, int64_t units)
+{
+    const int64_t shortest = (npiv + kSegMin - 1) / kSegMin;
+    const int64_t n = std::min(shortest * units, std::max<int64_t>(kContractUnits, units));
+    const size_t least = least_bytes(npiv, units);
+    return PartialBytes{std::max(least, (size_t)n * 256 * sizeof(double)), least};
+}
+
+static int64_t contract_units(int m_max, int nbins, int nmaps)
 {
     const int T = tiles_for(nbins);
-    return most_partials(npiv, (int64_t)nmaps * (m_max + 1) * (T * (T + 1) / 2)) * 256 * sizeof(double);
+    return (int64_t)nmaps * (m_max + 1) * (T * (T + 1) / 2);
+}
+
+PartialBytes contract_partial_bytes(int64_t npiv, int m_max, int nbins, int nmaps)
+{
+    return partial_bytes(npiv, contract_units(m_max, nbins, nmaps));
 }
 
 // Sums of the segments' partials, element by element, into segment 0 (in place: a block reads
@@ -695,10 +708,10 @@ static z3_status contract_src(int64_t npiv, int m_max, int nbins, int prec, int 
 {
     if (npiv <= 0 || nmaps <= 0) return Z3_OK;
     const int T = tiles_for(nbins), ntp = T * (T + 1) / 2;
-    const int seg = segment_pivots(npiv, (int64_t)nmaps * (m_max + 1) * ntp);
+    const int64_t units = contract_units(m_max, nbins, nmaps);
+    if (least_bytes(npiv, units) > partial_bytes) return fail(Z3_ERR_INVALID_ARG, "contraction workspace too small");
+    const int seg = segment_pivots(npiv, units, partial_bytes);
     int64_t nseg = (npiv + seg - 1) / seg;
-    if (contract_partial_bytes(npiv, m_max, nbins, nmaps) > partial_bytes)
-        return fail(Z3_ERR_INVALID_ARG, "contraction workspace too small");
     if (nseg > 65535) return fail(Z3_ERR_OVERFLOW, "too many pivots for one contraction (%lld)", (long long)npiv);
     if ((int64_t)nmaps * (m_max + 1) > 65535) return fail(Z3_ERR_OVERFLOW, "too many maps for one contraction");
     const bool f32 = prec == Z3_PREC_MIXED;
@@ -748,7 +761,7 @@ static z3_status contract_src(int64_t npiv, int m_max, int nbins, int prec, int 
         st = launch_pair(c, f32, true, nseg, s);
     }
     if (st == Z3_OK)
-        st = sum_segments(static_cast<double *>(partials), &nseg, (int64_t)nmaps * (m_max + 1) * ntp * 256, s);
+        st = sum_segments(static_cast<double *>(partials), &nseg, units * 256, s);
     if (st != Z3_OK) return st;
     const int total = nmaps * (m_max + 1) * nbins * nbins;
     hipLaunchKernelGGL(k_gram_reduce, dim3((total + 127) / 128), dim3(128), 0, s,
@@ -806,10 +819,10 @@ __global__ void k_cross_reduce(const double *part, int64_t nseg, int M1, int nb,
     z[1] += ir - ri;
 }
 
-size_t cross_partial_bytes(int64_t npiv, int m_max, int nbins)
+PartialBytes cross_partial_bytes(int64_t npiv, int m_max, int nbins)
 {
     const int T = tiles_for(nbins);
-    return most_partials(npiv, (int64_t)(m_max + 1) * T * T) * 256 * sizeof(double);
+    return partial_bytes(npiv, (int64_t)(m_max + 1) * T * T);
 }
 
 z3_status launch_contract_cross(int64_t npiv, int m_max, int nbins, int prec, const void *A1, const void *A2,
@@ -818,10 +831,11 @@ z3_status launch_contract_cross(int64_t npiv, int m_max, int nbins, int prec, co
 {
     if (npiv <= 0) return Z3_OK;
     const int T = tiles_for(nbins);
-    const int seg = segment_pivots(npiv, (m_max + 1) * T * T);
-    int64_t nseg = (npiv + seg - 1) / seg;
-    if (partial_bytes < cross_partial_bytes(npiv, m_max, nbins))
+    const int64_t units = (int64_t)(m_max + 1) * T * T;
+    if (least_bytes(npiv, units) > partial_bytes)
         return fail(Z3_ERR_INVALID_ARG, "multi-field contraction: partial buffer too small");
+    const int seg = segment_pivots(npiv, units, partial_bytes);
+    int64_t nseg = (npiv + seg - 1) / seg;
     PairArgs c = {};
     c.A1 = A1;
     c.A2 = A2;
@@ -836,7 +850,7 @@ z3_status launch_contract_cross(int64_t npiv, int m_max, int nbins, int prec, co
     c.seg = seg;
     c.part = static_cast<double *>(partials);
     z3_status st = launch_pair(c, prec == Z3_PREC_MIXED, false, nseg, s);
-    if (st == Z3_OK) st = sum_segments(static_cast<double *>(partials), &nseg, (int64_t)(m_max + 1) * T * T * 256, s);
+    if (st == Z3_OK) st = sum_segments(static_cast<double *>(partials), &nseg, units * 256, s);
     if (st != Z3_OK) return st;
     const int total = (m_max + 1) * nbins * nbins;
     hipLaunchKernelGGL(k_cross_reduce, dim3((total + 127) / 128), dim3(128), 0, s,

@@ -229,7 +229,7 @@ z3_status launch_contract(int64_t npiv, int m_max, int nbins, int prec, const vo
                           int64_t ldA, const double *piv_v, double *zeta, void *partials,
                           size_t partial_bytes, hipStream_t s);
 // nmaps contractions in one launch: map k reads A + k a_stride, piv_v + k v_stride and adds
-// into zeta + k z_stride; partials hold contract_partial_bytes(..., nmaps)
+// into zeta + k z_stride; partials hold contract_partial_bytes(..., nmaps).least or more
 z3_status launch_contract_maps(int64_t npiv, int m_max, int nbins, int prec, int nmaps, const void *A, int64_t ldA,
                                size_t a_stride, const double *piv_v, size_t v_stride, double *zeta, size_t z_stride,
                                void *partials, size_t partial_bytes, hipStream_t s);
@@ -244,8 +244,13 @@ bool gram_lds_fits(int m_max, int nbins, int prec);
 z3_status launch_contract_cross(int64_t npiv, int m_max, int nbins, int prec, const void *A1, const void *A2,
                                 int64_t ldA, const double *piv_v, double *zeta, void *partials,
                                 size_t partial_bytes, hipStream_t s);
-size_t cross_partial_bytes(int64_t npiv, int m_max, int nbins);
-size_t contract_partial_bytes(int64_t npiv, int m_max, int nbins, int nmaps = 1);
+// bytes of the partial sums of a contraction of up to npiv pivots: `want` fills the chip, and
+// with any less, down to `least`, the contraction takes longer segments
+struct PartialBytes {
+    size_t want, least;
+};
+PartialBytes cross_partial_bytes(int64_t npiv, int m_max, int nbins);
+PartialBytes contract_partial_bytes(int64_t npiv, int m_max, int nbins, int nmaps = 1);
 z3_status launch_weight_sum(const double *w, int64_t n, double *out, hipStream_t s);
 z3_status launch_pivot_values(const double *w, const double *x, int64_t n, double *v, hipStream_t s);
 z3_status launch_add_scalar(double *out, double value, hipStream_t s);
