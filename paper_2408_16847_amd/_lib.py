@@ -27,6 +27,7 @@ SIGNATURES = {
     "z3_index_set_batch_shape": (_I, [_P, _I, _I]),
     "z3_index_batch_shape": (_I, [_P, _I, _I, _P, _P]),
     "z3_index_free": (None, [_P]),
+    "z3_release_index_memory": (_I, []),
     "z3_accumulate_multipoles": (_I, [_P, _I, _I, _I, _I, _I64, _I64, _P, _P, _P, _P, _P, _P]),
     "z3_contract": (_I, [_I64, _I, _I, _I, _P, _P, _P, _P]),
     "z3_estimate": (_I, [_P, _I, _I, _I, _I64, _I64, _P, _P, _P]),

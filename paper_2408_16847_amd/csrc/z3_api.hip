@@ -395,6 +395,15 @@ Z3_API void z3_index_free(z3_index idx)
     if (idx) free_index(idx);
 }
 
+Z3_API z3_status z3_release_index_memory(void)
+{
+    int dev = 0;
+    z3_status st = check_hip(hipGetDevice(&dev), "hipGetDevice");
+    if (st == Z3_OK) st = wait_device(dev);
+    if (st == Z3_OK) release_idle(dev);
+    return st;
+}
+
 static z3_status check_common(const char *fn, const z3_index_s *idx, int map, int m_max, int prec,
                               int64_t p0, int64_t p1)
 {

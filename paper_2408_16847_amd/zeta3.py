@@ -131,6 +131,11 @@ class Index:
             pass
 
 
+def release_index_memory() -> None:
+    """Give the device memory kept from freed indexes back to the runtime (z3_release_index_memory)."""
+    _lib.call("z3_release_index_memory")
+
+
 def accumulate(idx: Index, m_max: int, p0: int = 0, p1: int | None = None, prec="fp64", norm="bin",
                map_index: int = 0, want_a=True, want_w=False, want_counts=False, want_idhash=False,
                pair_total=None):

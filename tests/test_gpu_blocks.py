@@ -2,6 +2,7 @@
 is being captured): no other index may get it before the work that reads it has ended."""
 
 import ctypes
+import time
 
 import numpy as np
 import pytest
@@ -73,3 +74,27 @@ def test_index_freed_while_another_stream_captures():
     third.set_values(x)
     assert torch.equal(z3.estimate_raw(third, M).cpu(), expect[0])
     third.free()
+
+
+def test_memory_of_freed_indexes_can_be_given_back():
+    G.say("case: index memory given back")
+    xyz = ring_centres(256).cuda()
+    n = xyz.shape[1]
+    x = torch.zeros(n, dtype=torch.float64, device="cuda")
+    z3.release_index_memory()
+    torch.cuda.synchronize()
+    time.sleep(0.5)  # the driver's figure follows a free with some delay
+    before = torch.cuda.mem_get_info()[0]
+    idx = z3.Index(xyz, chord2_edges(theta_edges(arcmin(60.0), arcmin(600.0), 8, True)))
+    idx.set_values(x)
+    idx.free()
+    held = before - torch.cuda.mem_get_info()[0]
+    G.say("  held after the index was freed:", held)
+    assert held > 100 * n  # 64 B of records a point alone, and the build's arrays
+    z3.release_index_memory()
+    for _ in range(40):
+        held = before - torch.cuda.mem_get_info()[0]
+        if held < 8 << 20:
+            break
+        time.sleep(0.05)
+    assert held < 8 << 20  # the runtime's own rounding at most
