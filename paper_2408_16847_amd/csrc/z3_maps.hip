@@ -17,6 +17,11 @@ namespace z3 {
 // Nside 512 at m_max = 10 139.6 -> 107.0 ms an estimate, Nside 128 2.39 -> 1.43 ms (there on
 // lists, 1.58 band by band).
 //
+// Four maps' values requested ahead spill in the candidate loop from m_max 5 on at three waves per
+// SIMD, and at m_max 11 on lists also at two; the first run at two waves from there, the last
+// loads them when a pair is found (Nside 192, 5 bins of 28 to 300 pairs, four maps: m_max 5 2386 ->
+// 1672 us, 6 3836 -> 1784 us, 11 4606 -> 3741 us).  Two maps at m_max 12 likewise (4390 -> 3602 us).
+//
 // K = 3 when the caller reads at most the first three maps of the group, else 4 up to m_max =
 // kTileMmax; beyond, the 2 K (2 m_max + 1) registers of four maps' sums no longer fit beside the
 // requests, and blockIdx.z takes the group two maps at a time (Nside 128, m_max = 16: 15.4 ->
@@ -24,7 +29,10 @@ namespace z3 {
 // = 16, but from 13 on not the values requested ahead (they are loaded when a pair is found),
 // and from 15 on not the record either.
 constexpr int kTileMmax = 11;
-template <int M, int K> constexpr bool maps_values_ahead() { return K != 3 || M <= 12; }
+template <int M, int K, bool LIST> constexpr bool maps_values_ahead()
+{
+    return K == 2 || (K == 3 ? M <= 12 : M <= (LIST ? 10 : 11));
+}
 template <int M, int K> constexpr bool maps_record_ahead() { return K != 3 || M <= 14; }
 
 struct MapArgs {
@@ -51,7 +59,7 @@ struct MapArgs {
 template <int M, int K>
 constexpr int maps_waves_per_eu()
 {
-    return M <= (K == 2 ? 12 : 6) ? 3 : 2;
+    return M <= (K == 2 ? 11 : (K == 3 ? 6 : 4)) ? 3 : 2;
 }
 
 template <int M, bool F32OUT, int K, bool LIST>
@@ -122,7 +130,7 @@ void k_multipoles_maps(MapArgs a)
 
         // one candidate: its record r, its byte offset o of the window's records and the group's
         // values, requested `ahead` or loaded when the pair is found
-        constexpr bool AHEAD = maps_values_ahead<M, K>();
+        constexpr bool AHEAD = maps_values_ahead<M, K, LIST>();
         auto cand = [&](const double4 &r, const double4 &ahead, uint32_t o, __amdgpu_buffer_rsrc_t vband,
                         __amdgpu_buffer_rsrc_t wband) __attribute__((always_inline)) {
             const double dx = r.x - xp, dy = r.y - yp, dz = r.z - zp;
