@@ -208,7 +208,8 @@ constexpr int adjoint_waves_per_eu()
 }
 
 // Whether the next candidate's record is requested while the current one is worked on: where its
-// 8 registers do not spill at that occupancy.
+// 8 registers do not spill at that occupancy.  (Four maps a lane, with against without: 0-2% faster or
+// slower at m_max 2, 6, 8 and 9; at 4 5% faster where windows are long, 5% slower where short.)
 template <int M, int K>
 constexpr bool adjoint_record_ahead()
 {
@@ -413,10 +414,14 @@ static void launch_scatter_one(const ScatterArgs &a, int nm, bool planar, hipStr
 }
 
 template <int M>
-static void launch_scatter_m(const ScatterArgs &a, int nm, bool planar, bool join, hipStream_t s)
+static void launch_scatter_m(const z3_index_s *idx, const ScatterArgs &a, int nm, hipStream_t s)
 {
-    auto from = [&](int first) {
+    const bool planar = idx->planar;
+    // maps [first, ..), `rows` grid rows of them (the bins split as far as all the rows' blocks
+    // leave the chip idle)
+    auto part = [&](int first, int rows) {
         ScatterArgs b = a;
+        b.groups = bin_groups(idx, (int64_t)a.nblocks * rows);
         b.pv += (size_t)first * a.n_stride;
         b.grad += (size_t)first * a.n_stride;
         b.rec += (size_t)first * a.rec_stride;
@@ -426,17 +431,22 @@ static void launch_scatter_m(const ScatterArgs &a, int nm, bool planar, bool joi
     const int ones = planar ? nm : nm & 1;  // planar: one map per lane, one grid row per map
     if (!planar) {
         constexpr int K = M <= 11 ? 4 : 2;
-        if (nm >= K)
-            hipLaunchKernelGGL((k_adjoint_scatter<M, K, false, false>), dim3(a.nblocks, nm / K, a.groups.n), dim3(kBlock),
-                               0, s, a);
+        if (nm >= K) {
+            const ScatterArgs b = part(0, nm / K);
+            hipLaunchKernelGGL((k_adjoint_scatter<M, K, false, false>), dim3(b.nblocks, nm / K, b.groups.n), dim3(kBlock),
+                               0, s, b);
+        }
         if constexpr (K == 4)
-            if (nm & 2)
-                hipLaunchKernelGGL((k_adjoint_scatter<M, 2, false, false>), dim3(a.nblocks, 1, a.groups.n), dim3(kBlock), 0,
-                                   s, from(nm & ~3));
+            if (nm & 2) {
+                const ScatterArgs b = part(nm & ~3, 1);
+                hipLaunchKernelGGL((k_adjoint_scatter<M, 2, false, false>), dim3(b.nblocks, 1, b.groups.n), dim3(kBlock), 0,
+                                   s, b);
+            }
     }
     if (ones) {
-        if (join) launch_scatter_one<M, true>(from(nm - ones), ones, planar, s);
-        else launch_scatter_one<M, false>(from(nm - ones), ones, planar, s);
+        const ScatterArgs b = part(nm - ones, ones);
+        if (short_windows(idx)) launch_scatter_one<M, true>(b, ones, planar, s);
+        else launch_scatter_one<M, false>(b, ones, planar, s);
     }
 }
 
@@ -491,10 +501,9 @@ static z3_status adjoint_chunk_maps(z3_index idx, int map, int nm, int m_max, in
     sa.n_stride = (size_t)idx->n;
     sa.rec_stride = (size_t)2 * idx->n;
     sa.d_stride = stride;
-    sa.groups = bin_groups(idx, sa.nblocks);
     sa.px0 = idx->plane_x0; sa.py0 = idx->plane_y0; sa.psx = idx->plane_sx;
     switch (m_max) {
-#define Z3_CASE(MM) case MM: launch_scatter_m<MM>(sa, nm, idx->planar, short_windows(idx), s); break;
+#define Z3_CASE(MM) case MM: launch_scatter_m<MM>(idx, sa, nm, s); break;
         Z3_CASE(0) Z3_CASE(1) Z3_CASE(2) Z3_CASE(3) Z3_CASE(4) Z3_CASE(5) Z3_CASE(6) Z3_CASE(7)
         Z3_CASE(8) Z3_CASE(9) Z3_CASE(10) Z3_CASE(11) Z3_CASE(12) Z3_CASE(13) Z3_CASE(14)
         Z3_CASE(15) Z3_CASE(16)
