@@ -166,7 +166,10 @@ struct BinGroups {
     unsigned char first[Z3_MAX_NBINS + 1];
 };
 BinGroups bin_groups(const z3_index_s *idx, int64_t nblk);
-bool short_windows(const z3_index_s *idx);  // windows of few pairs (z3_multipoles.hip)
+// Windows (z3_multipoles.hip): their mean pairs at the mean density of the colatitude range, or of
+// its occupied longitudes; and whether the first makes them short
+double pairs_a_window(const z3_index_s *idx, bool occupied);
+bool short_windows(const z3_index_s *idx);
 
 // multipole kernels (z3_multipoles.hip)
 // Pivot positions: either the index's own points (index order) or an external catalogue.

@@ -276,6 +276,19 @@ void k_multipoles_maps(MapArgs a)
     }
 }
 
+// Whether the launch walks window lists: as in k_multipoles, but four maps at m_max 11 and three at 16,
+// which spill in the lists' candidate loop, only below one pair a window, and by the density where
+// the points are.  Lists / band by band, three maps at 16 and four at 11, us: at 0.8 pairs a window
+// (Nside 192) 1597 / 1662 and 1581 / 1527, at 1.2 3857 / 3902 and 3780 / 3489, at 4.6 3862 / 3295 and 3730 /
+// 2833; on a pixelised patch of 54,000 points at 99 (7.5 by the density of the colatitude range) 5377 /
+// 3689 and 5187 / 2887.
+constexpr double kShortSpilled = 1.0;
+static bool walk_lists(const z3_index_s *idx, int m_max, int nslots)
+{
+    const bool spills = nslots <= 3 ? m_max == 16 : m_max == 11;
+    return spills ? pairs_a_window(idx, true) < kShortSpilled : short_windows(idx);
+}
+
 template <int M, bool LIST>
 static void launch_maps_ml(bool f32out, int nslots, const MapArgs &a, hipStream_t s)
 {
@@ -325,7 +338,7 @@ z3_status launch_multipoles_maps(const z3_index_s *idx, int group, int nslots, i
     a.nblocks = (int)nblk;
     a.groups = bin_groups(idx, nblk);
     const bool f32 = prec == Z3_PREC_MIXED;
-    const bool lists = short_windows(idx);
+    const bool lists = walk_lists(idx, m_max, nslots);
     hipEvent_t ev0;
     profile_begin(s, &ev0);
     switch (m_max) {

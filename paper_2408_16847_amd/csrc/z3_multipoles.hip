@@ -65,14 +65,16 @@ static void launch_m(bool planar, bool mixed, bool ids, bool self, const MultArg
 // low: 1.04-1.32; jittered plane grids at 3.8: 1.14-1.20, 9.3: 1.03.  The line is set at 8.
 constexpr double kShortWindow = 8.0;
 
-bool short_windows(const z3_index_s *idx)
+double pairs_a_window(const z3_index_s *idx, bool occupied)
 {
     const EdgeTab &t = idx->edges;
     const int nb = idx->nbins;
     double windows = 0.0;
     for (int b = 1; b <= nb; ++b) windows += 4.0 * t.rad_out[b] / idx->band_h + 2.0;
-    return idx->density * kPi * (t.e[nb] - t.e[0]) < kShortWindow * windows;
+    return idx->density / (occupied ? idx->sky_part : 1.0) * kPi * (t.e[nb] - t.e[0]) / windows;
 }
+
+bool short_windows(const z3_index_s *idx) { return pairs_a_window(idx, false) < kShortWindow; }
 
 z3_status launch_multipoles(const z3_index_s *idx, Pivots piv, int map, int m_max, int prec, int norm,
                             int64_t p0, int64_t p1, void *A, int64_t ldA, double *W,
