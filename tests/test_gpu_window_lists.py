@@ -60,3 +60,30 @@ def test_plane():
         idx = z3.Index(xy.cuda(), E, cell_size=cell, planar=True)
         idx.set_values(torch.randn(xy.shape[1], dtype=torch.float64, device="cuda"))
         _check(idx, 9, "fp64", [(0, xy.shape[1])])
+
+
+@pytest.mark.parametrize("lo,hi,nb", [(1.5, 8.0, 10), (3.0, 20.0, 6), (12.0, 30.0, 2)])
+@pytest.mark.parametrize("radius", [12.0, 40.0])
+def test_pixelised_patch(lo, hi, nb, radius):
+    # a patch's density over its colatitude range reads low: real windows of 3 to 70 pairs, which the rule
+    # reads as 0.5 to 30, so that these cases lie on both sides of its line
+    G.say("case: window lists, patch", lo, hi, nb, radius)
+    ring = ring_centres(48).numpy()
+    centre = np.array([math.cos(0.5), 0.0, math.sin(0.5)])
+    xyz = np.ascontiguousarray(ring[:, centre @ ring > math.cos(radius * DEG)])
+    n, pixel = xyz.shape[1], 60.0 / 48 * DEG
+    x = np.random.default_rng(11).normal(size=n)
+    E = chord2_edges(theta_edges(lo * pixel, hi * pixel, nb, True))
+    idx = G.build(xyz, x, E)
+    _check(idx, 8, "fp64", [(0, n), (n // 2, n // 2 + 70)])
+    p0 = n // 3
+    a, W, N, H = G.gpu_multipoles(idx, 8, p0, p0 + 40, norm="none")
+    lists = z3.accumulate(idx, 8, p0, p0 + 40, norm="none", want_counts=True)
+    ao, Wo, No, _, Ho = G.oracle_multipoles(xyz, x, np.ones(n), E, 8, G.perm(idx)[p0:p0 + 40])
+    assert np.array_equal(N, No) and np.array_equal(H, Ho)
+    assert np.array_equal(lists["counts"].cpu().numpy().T, No)
+    A = lists["A"].cpu().numpy()
+    got = np.transpose(A[:, 0] + 1j * A[:, 1], (2, 0, 1))
+    # sums of at most 2,500 values of size one, harmonics good to ~1e-14
+    assert np.abs(got - ao).max() < 1e-10
+    idx.free()
