@@ -222,12 +222,13 @@ constexpr bool adjoint_record_ahead()
 // maps.
 constexpr int kAggSlots = 1024;
 
-//
 // What bounds it: the FP64 work of a pair (about 60 operations) in lanes that wait for the
 // longest window of their wave, and the latency of the records.  JOIN walks a window's two segments
 // as one, so that lanes even out over their sum: 786,000 pixels x 15 bins (m_max 10, windows of 4 pairs)
 // 7.26 -> 6.92 ms a gradient; with windows of 9 and more pairs the bookkeeping costs more than that (3 maps, 6
-// bins to 400', 21.6 -> 24.0 ms a gradient).  Several bands at a time took the gain back.  With four or two maps
+// bins to 400', 21.6 -> 24.0 ms a gradient).  The rule (short_windows) reads a pixelised patch's windows short:
+// joined, a patch's gradient takes 0.87-1.10 of the other form's time at 4 to 22 real pairs a window, 1.06-1.49 at
+// 40 to 176.  Several bands at a time took the gain back.  With four or two maps
 // a lane the two forms are equal, and only the plain one is built.
 template <int M, int K, bool PLANAR, bool JOIN>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(adjoint_waves_per_eu<M, K>())))

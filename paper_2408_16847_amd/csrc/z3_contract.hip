@@ -530,10 +530,11 @@ bool gram_lds_fits(int m_max, int nbins, int prec)
            gram_tile_bytes(nbins, R, prec == Z3_PREC_MIXED) + kGramKP * sizeof(double) <= kGramLdsMax;
 }
 
-// element (pivot p, bin b, row r) of map j at base + j map_stride + p sp + b sb + r sr
+// element (pivot p, bin b, row r) of map j: pivot-major staging at base + j map_stride + p sp + b sb + r,
+// pivot-minor multipoles at base + j map_stride + (r nb + b) sb + p
 struct GramSrc {
     const void *base;
-    int64_t sp, sb, sr;
+    int64_t sp, sb;
     size_t map_stride;
 };
 
@@ -773,7 +774,7 @@ z3_status launch_contract_maps(int64_t npiv, int m_max, int nbins, int prec, int
                                size_t a_stride, const double *piv_v, size_t v_stride, double *zeta, size_t z_stride,
                                void *partials, size_t partial_bytes, hipStream_t s)
 {
-    const GramSrc src{A, 1, ldA, (int64_t)nbins * ldA, a_stride};
+    const GramSrc src{A, 1, ldA, a_stride};
     return contract_src(npiv, m_max, nbins, prec, nmaps, src, false, piv_v, v_stride, zeta, z_stride, partials,
                         partial_bytes, s);
 }
@@ -783,7 +784,7 @@ z3_status launch_contract_staged(int64_t npiv, int m_max, int nbins, int prec, i
                                  size_t partial_bytes, hipStream_t s)
 {
     const int64_t R = 2 * (m_max + 1);
-    const GramSrc src{stage, (int64_t)nbins * nmaps * R, (int64_t)nmaps * R, 1, (size_t)R};
+    const GramSrc src{stage, (int64_t)nbins * nmaps * R, (int64_t)nmaps * R, (size_t)R};
     return contract_src(npiv, m_max, nbins, prec, nmaps, src, true, piv_v, v_stride, zeta, z_stride, partials,
                         partial_bytes, s);
 }
