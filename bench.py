@@ -28,7 +28,37 @@ METRIC = "pair-multipole updates/s; ζ_m wall time Nside=2048, mixed vs FP64 at 
 # against the FP64 vector peak
 PEAK_VALU_TFLOPS = {"mixed": 78.6, "fp64": 78.6}
 PEAK_MFMA_TFLOPS = {"mixed": 157.3, "fp64": 78.6}  # dense FP32 / FP64 matrix cores
-FLOPS_PER_UPDATE = 12.5  # algorithmic flops per (pair, m) at m_max = 10: 10 per m + ~35 per pair / 11
+
+
+def pair_geometry_flops():
+    """Flops (an FMA counts 2) of a pair's geometry in the multipole kernels: separation 3, squared chord 5,
+    north and east coordinates 8, their length 4, its refined reciprocal 6, the unit bearing 2."""
+    return 28
+
+
+def one_map_flops(m_max, plane=False, self_pairs=True):
+    """Flops of a pair in k_multipoles: the geometry (two coordinates less on a plane), the sums over
+    products of two short factors, and the sum of squares that removes the self pairs."""
+    h = m_max if m_max <= 4 else (m_max + 1) // 2
+    r = m_max - h
+    sums = 1
+    if m_max >= 1:
+        sums += 2 * max(h - 1, 0) + 2 + 4 * (h - 1) + (2 if r == 0 else 4 + 2 * r + 2 * (r - 1))
+    return pair_geometry_flops() - (11 if plane else 0) + sums + (0 if self_pairs else 2)
+
+
+def group_flops(m_max, nmaps):
+    """Flops of a pair in k_multipoles_maps for `nmaps` maps of one group: geometry and chain once, then
+    every map's sums."""
+    per_map = 1 if m_max == 0 else 5 + 4 * (m_max - 1)
+    return pair_geometry_flops() + 2 * max(m_max - 1, 0) + nmaps * per_map
+
+
+def map_passes(nmaps):
+    """Maps of each pass of the register-tiled path: groups of four, one or two left over alone."""
+    rest = nmaps % 4 if nmaps % 4 <= 2 else 0
+    groups = [min(4, nmaps - g) for g in range(0, nmaps - rest, 4)] if nmaps > 2 else []
+    return groups, nmaps - sum(groups)
 
 
 def log(*a):
@@ -45,7 +75,8 @@ def cpu_model():
     return "unknown"
 
 
-KERNEL_SOURCES = ("z3_multipoles.hip", "z3_device.h")  # the kernel and its device helpers
+# the kernel, its launches and its device helpers
+KERNEL_SOURCES = ("z3_multipoles_device.h", "z3_multipoles.hip", "z3_multipoles_list.hip", "z3_device.h")
 TRAFFIC_JSON = os.path.join(ROOT, "profiles", "k_multipoles_traffic.json")
 
 
@@ -421,8 +452,11 @@ def main():
         # 3 to 56 / 24 maps), whose pair geometry is shared by the maps of a lane
         rf_kernel = "k_multipoles_maps" if (args.cross or cfg.nmaps > 2) else "k_multipoles"
         rf_bound, rf_peak = "alu", PEAK_VALU_TFLOPS[main_prec]
-        rf_flops = FLOPS_PER_UPDATE * updates
-        rf_unit_note = f"{FLOPS_PER_UPDATE} flop per pair-multipole update"
+        # the operations of the kernel's own arithmetic for the pairs in the bins
+        groups, ones = ([3], 0) if args.cross else map_passes(cfg.nmaps)
+        per_pair = sum(group_flops(M, k) for k in groups) + ones * one_map_flops(M, cfg.kind == "plane", self_pairs)
+        rf_flops = float(per_pair) * r["pairs"]
+        rf_unit_note = f"{per_pair} flop per pair (pairs in bins, an FMA counts 2)"
     achieved = rf_flops / kern_s_per_step / 1e12 if kern_s_per_step > 0 else None
     out = {
         "metric": METRIC,
@@ -590,7 +624,7 @@ def nside4096_record(z3, torch):
             idx.free()
             zs[prec] = zh[..., 0] + 1j * zh[..., 1]
             updates = npairs * (M + 1)
-            ach = FLOPS_PER_UPDATE * updates / (kms / 1e3) / 1e12 if kms > 0 else None
+            ach = one_map_flops(M) * npairs / (kms / 1e3) / 1e12 if kms > 0 else None
             sub[prec] = {"zeta_wall_s": dt, "pairs": npairs, "updates_per_s": updates / dt,
                          "k_multipoles_ms": kms, "launches": launches,
                          "roofline_frac": ach / PEAK_VALU_TFLOPS[prec] if ach else None,
@@ -692,9 +726,9 @@ def fftlog_bench(args, z3, torch):
     launches, kms = z3.profile_read(reset=True)
     z3.profile_enable(False)
     ns = S["N"] + 1
-    flops_launch = 8.0 * S["ntheta"] * ns * (S["N"] // 2 + 1) * nm
-    kern_s = kms / max(launches, 1) / 1e3
-    achieved = flops_launch / kern_s / 1e12 if kern_s > 0 else None
+    flops_step = 3 * 8.0 * S["ntheta"] * ns * (S["N"] // 2 + 1) * nm  # three factor pairs
+    kern_s = kms / args.steps / 1e3
+    achieved = flops_step / kern_s / 1e12 if kern_s > 0 else None
     total_flops = nm * 3 * (4.0 * ns * S["nchi"] + 8.0 * S["ntheta"] * ns * (S["N"] // 2 + 1)
                             + 4.0 * S["ntheta"] ** 2 * ns)
     log(f"[bench] fftlog: {nm} models in {dt * 1e3:.2f} ms/step; k_cgemm<2> {kms / max(launches, 1):.3f} ms "
@@ -734,7 +768,7 @@ def fftlog_bench(args, z3, torch):
                      "peak": PEAK_MFMA_TFLOPS["fp64"], "unit": "TFLOP/s",
                      "frac": achieved / PEAK_MFMA_TFLOPS["fp64"] if achieved else None, "traffic": None,
                      "avg_launch_ms": kms / max(launches, 1), "launches_per_step": launches / args.steps,
-                     "flops": "8 ntheta (N+1) (N/2+1) flop per product (omega U1) H and model"},
+                     "flops": "8 ntheta (N+1) (N/2+1) flop per product (omega U1) H, factor pair and model"},
         "cpu_baseline": {"value": ns_cpu / t_cpu, "unit": "models/s", "cores": threads, "kind": "oracle",
                          "sample": f"the first {ns_cpu} models, one oracle call each (NumPy, BLAS threads)",
                          "seconds": t_cpu, "gpu_max_err_on_sample": err},
