@@ -206,12 +206,17 @@ z3_status gather_pivots(const int *perm, int64_t len, Pivots piv, int64_t p0, co
                         double *gx, double *gy, double *gz, double *gv, hipStream_t s);
 
 // Many maps over one set of positions: the MFMA kernel (one block per pivot, every map at
-// once) or passes of the register-tiled kernel over the groups of kMapGroup maps.  Measured,
-// estimator calls at m_max = 10 and 15 bins, groups / MFMA in ms: 300,000 pivots of the Nside 512
-// map mixed 16 maps 47 / 75, 24 maps 71 / 88, 64 maps ~189 / 122; FP64 32 maps 95 / 141, 56 maps
-// 167 / 210, 64 maps ~191 / 191; the Nside 128 map mixed 24 maps 8.5 / 10.9, 64 maps ~22.6 / 20.6;
-// FP64 56 maps 22.0 / 25.6, 64 maps ~25 / 27.  The groups are faster up to about 28 maps on the
-// mixed path and 60 on the FP64 one; the lines stand at 24 and 56, which the interface states.
+// once) or passes of the register-tiled kernel over the groups of kMapGroup maps.  Measured on
+// either side of the lines, estimator calls with 15 bins, groups / MFMA (the best fixed shape) in ms:
+//   300,000 pivots of the Nside 512 map, m_max = 10: mixed 24 maps 71 / 88, 32 94 / 90, 64 187 / 138;
+//     FP64 48 maps 143 / 210, 56 168 / 211, 64 192 / 213;
+//   the Nside 128 map, m_max = 10: mixed 24 8.5 / 11.0, 32 11.4 / 11.9, 64 22.8 / 20.5; FP64 56 22.1 /
+//     26.1, 64 25.2 / 27.8;
+//   m_max = 4, Nside 512: mixed 24 52 / 66, 32 69 / 67; FP64 56 122 / 139, 64 139 / 140;
+//   m_max = 12 (two maps at a time): mixed 16 72 / 77, 24 108 / 90; FP64 32 147 / 143, 56 256 / 213;
+//   m_max = 16, 150,000 pivots: mixed 24 62 / 87, 32 84 / 88, 64 165 / 145; FP64 56 147 / 205, 64 168 / 208.
+// Break-even lies near 30 maps on the mixed path and from 64 on the FP64 one, at m_max = 12 near 20
+// and 32; the lines stand at 24 and 56, which the interface states.
 // A block shape fixed by the caller
 // (z3_index_set_batch_shape) selects the MFMA kernel for more than kMapGroup maps.
 inline bool many_maps_on_mfma(const z3_index_s *idx, int prec)

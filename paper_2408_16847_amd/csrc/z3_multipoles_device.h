@@ -154,9 +154,9 @@ struct HarmonicSums {
 };
 
 // Occupancy target of the multipole kernel (waves per SIMD that the register allocation
-// aims for).  Measured on MI355X at m_max = 10: 4 waves beat 3 by ~15% despite a couple
-// of spilled registers; from m_max = 11 the sums need more registers, and 3 waves hold them
-// without spills up to m_max = 16.
+// aims for).  Measured on MI355X at m_max = 10: 4 waves beat 3 by ~15% although up to 33
+// registers of the band loop spill; from m_max = 11 the sums need more registers, and 3 waves hold
+// them (a few of the band loop's spill from m_max = 12 on, 23 at 16).
 #ifndef Z3_MULT_WAVES_PER_EU
 #define Z3_MULT_WAVES_PER_EU 4
 #endif
