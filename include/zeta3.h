@@ -191,8 +191,9 @@ z3_status z3_build_index_planar(int64_t n, const double *xy, const double *w, in
 /*
  * Release an index and its device memory (NULL is ignored).  Waits for the device's work.  The
  * library keeps up to 4 GiB of such memory per device for the next index; it gives it back
- * when an allocation of its own fails, and by z3_release_index_memory.  Where the runtime refuses the wait (while a stream is
- * being captured), the memory goes to no other index until a later wait has succeeded.
+ * when an allocation of its own fails, and by z3_release_index_memory.  Where the runtime
+ * refuses the wait (while a stream is being captured), the memory goes to no other index until a
+ * later wait has succeeded.
  */
 void z3_index_free(z3_index idx);
 
